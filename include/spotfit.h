@@ -47,7 +47,7 @@
  * Asynchrony: work is enqueued on the stream and the call returns; results
  * are valid after the stream is synchronised.  Calls on one context are not
  * thread-safe against each other, and must not overlap on the device: the
- * double-precision kernel hands spots out through a counter the context owns
+ * double-precision kernel hands spots out through counters the context owns
  * (and the mixed schedule through its workspace), so concurrent streams each
  * need their own context (as the serving loop keeps one per stream).
  */
@@ -97,31 +97,24 @@ typedef enum {
                              double; FP32 profile, FP64 determinant and LM solve      */
 } spotfit_precision_t;
 
-/* How the separable kernel maps a batch onto lane groups. */
+/* How the separable kernel goes through a batch. */
 typedef enum {
-  SPOTFIT_SCHEDULE_UNIFORM = 0, /* one group width for the whole batch, chosen by max_side;
-                                   spots are strided over a persistent grid            */
-  SPOTFIT_SCHEDULE_MIXED = 1    /* batches of uneven sizes: a classify pass buckets spots
-                                   by size class (largest side <= 8, <= 16, <= 32), then
-                                   one persistent launch runs each class with its own
-                                   group width; needs the context workspace (see
-                                   spotfit_ctx_reserve)                                 */
+  SPOTFIT_SCHEDULE_UNIFORM = 0, /* spots in the order given                             */
+  SPOTFIT_SCHEDULE_MIXED = 1    /* batches of uneven sizes: a classify pass sorts larger
+                                   batches by side first, so that spots evaluated
+                                   together have one size; needs the context workspace
+                                   (see spotfit_ctx_reserve); the same bits             */
 } spotfit_schedule_t;
 
-/* Which lane mapping the double-precision kernel uses. */
+/* Which mapping the double-precision kernel uses.  Both hints run the matrix-core
+ * kernel, with 4, 16 or 64 spots per wavefront by the size of the batch: 4 for
+ * the shortest steps (a camera frame), 64 for the most spots per second.  A
+ * spot's result does not depend on that, nor on the batch it is in. */
 typedef enum {
-  SPOTFIT_PLAN_THROUGHPUT = 0, /* default: the most spots per second for batches that fill
-                                  the GPU.  Spots up to 16x16 px: 4-lane groups that fit 4
-                                  spots at once, one per lane; larger spots: 16-lane groups
-                                  of 4 spots.  A batch too small to give every resident spot
-                                  slot 1.5-2.5 spots (about 200k-330k spots up to 16 px, 80k
-                                  above, on 256 CUs) takes 4 or 16 lanes per spot instead
-                                  (the same bits)                                        */
-  SPOTFIT_PLAN_LATENCY = 1     /* one lane per column (8, 16 or 32 lanes per spot): each
-                                  evaluation step is shorter, so a batch too small to
-                                  fill the GPU (a camera frame) finishes sooner; results
-                                  agree with the other plan in every decision but may
-                                  differ in the last bits                               */
+  SPOTFIT_PLAN_THROUGHPUT = 0, /* default; spotfit_autotune may keep another mapping, whose
+                                  results agree in every decision but may differ in the
+                                  last bits                                              */
+  SPOTFIT_PLAN_LATENCY = 1     /* never another mapping                                  */
 } spotfit_plan_hint_t;
 
 typedef enum {
@@ -201,7 +194,7 @@ int spotfit_fit_spots(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
  * context and options), but the fit's scratch memory -- the spot counter of
  * the uniform schedule, the counters and size-class lists of the mixed
  * schedule -- is a fixed array of the library in device memory instead of the
- * context's workspace.  The array is 4 * (200 + 3 * SPOTFIT_NOALLOC_MAX_SPOTS)
+ * context's workspace.  The array is 4 * (1160 + 3 * SPOTFIT_NOALLOC_MAX_SPOTS)
  * bytes (about 12.6 MB) on every GPU the library runs on, held until the
  * process ends; its address on a device is looked up when the first context
  * on that device is created.  The call allocates nothing and never grows the
@@ -254,23 +247,18 @@ int spotfit_peak_init(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
                       const spotfit_shape_t* sizes, const int64_t* offsets, int64_t n_spots,
                       const spotfit_options_t* opt, float* init_out, void* stream);
 
-/* Raw spots in, fits out, in one launch: the start values of
+/* Raw spots in, fits out, in one call: the start values of
  * spotfit_moment_init and the fit from them (the paper leaves start values to
  * the caller, Results section; its fit is the Fit2DGaussian algorithm with
- * Eqs. 5-14).  With opt->precision SPOTFIT_PREC_FP64 and a batch that the
- * narrow or wide plans fit (the latency hint, or too few spots for the
- * lane-owned plans of SPOTFIT_PLAN_THROUGHPUT), the fit kernel's own lane
- * groups compute each spot's start values before they fit it, so no
- * start-value pass and no round trip through memory sits between frame and
- * fit; a batch that takes a lane-owned plan, and the other precisions, get a
- * start-value launch first (for the lane-owned plans the faster way).
+ * Eqs. 5-14): a start-value launch, then the fit's.  (The narrow and wide
+ * plans, where spotfit_autotune or an override chose one, compute each spot's
+ * start values in the fit's launch.)
  * init_out float[n][4] (device, caller-owned, required) receives the start
  * values each fit began from (NaN for the shapes spotfit_moment_init rejects,
- * whose fits end as BAD_INPUT).  They equal spotfit_moment_init's up to the
- * order of its double-precision sums (bit for bit where the fit's lanes per
- * spot match the start-value kernel's: the default plans of the uniform
- * schedule), and the fit outputs are bit for bit those of spotfit_fit_spots
- * with init = init_out and the same plan.  The other arguments, ownership,
+ * whose fits end as BAD_INPUT).  They equal spotfit_moment_init's (with such
+ * other plans: up to the order of its double-precision sums), and the fit
+ * outputs are bit for bit those of spotfit_fit_spots with init = init_out and
+ * the same plan.  The other arguments, ownership,
  * stream and return codes as spotfit_fit_spots. */
 int spotfit_fit_raw(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
                     const spotfit_shape_t* sizes, const int64_t* offsets, int64_t n_spots,
@@ -351,10 +339,9 @@ typedef struct {
  * nothing.  The mixed schedule's workspace (12 bytes per spot plus 32) belongs
  * to the graph: allocated here, freed in spotfit_graph_destroy, so later calls
  * on the context (which may grow the context's own workspace) leave it alone.
- * Replays use the context's spot counter: do not overlap them with other calls
+ * Replays use the context's spot counters: do not overlap them with other calls
  * on the same context.  init may be NULL: the graph then computes the start values on
- * the device as spotfit_fit_raw does (inside the fit's launch for the
- * double-precision kernels), into a buffer of n x 4 floats it allocates here
+ * the device as spotfit_fit_raw does, into a buffer of n x 4 floats it allocates here
  * and frees in spotfit_graph_destroy, so that a replay takes raw pixels to
  * fits (io->init must then be NULL).  n_spots must be > 0.  Returns SPOTFIT_OK
  * or a negative spotfit_error_t. */

@@ -31,6 +31,8 @@ struct spotfit_ctx {
   int mixed_plan;
   bool mixed_forced;  // set by the SPOTFIT_MIXED_PLAN override
   int occ_mixed[8];
+  int occ_matrix[3][2];  // matrix-core kernel: by spots per wavefront (4, 16, 64) and width
+  int matrix_slots;      // SPOTFIT_MATRIX_SLOTS override: 4, 16 or 64; else 0
   int32_t* ws;      // counters[8] then 3 lists of ws_cap spot indices
   int64_t ws_cap;
   unsigned long long* stats;  // device histogram buffer of spotfit_get_stats
@@ -38,14 +40,13 @@ struct spotfit_ctx {
   int32_t* scratch;           // device address of this device's copy of `scratch` (below)
 };
 
-// Scratch memory of spotfit_fit_spots_noalloc: word 0 the uniform schedule's
-// spot counter; from word 64 (256 bytes in) the mixed schedule's workspace: 8
-// counters, the classify pass's 128 words, then its 3 size-class lists of
+// Scratch memory of spotfit_fit_spots_noalloc: first the spot counters (one
+// cache line each), then the mixed schedule's workspace: 8 counters, the classify pass's 128 words, then its 3 size-class lists of
 // SPOTFIT_NOALLOC_MAX_SPOTS spot indices.  Every GPU
 // holds its own copy at its own address.  In host code this name only stands
 // for the array: kernels get the address that hipGetSymbolAddress returns for
 // the current device (kept per device in g_scratch_addr and in each context).
-constexpr int64_t kScratchMixedAt = 64;
+constexpr int64_t kScratchMixedAt = sf::kMatrixCounters * sf::kMatrixCounterWords;
 constexpr int64_t kScratchWords = kScratchMixedAt + sf::kMixedHeadWords + 3 * (int64_t)SPOTFIT_NOALLOC_MAX_SPOTS;
 static __device__ __align__(256) int32_t scratch[kScratchWords];
 
@@ -87,6 +88,11 @@ hipError_t scratch_address(int device, int32_t** out) {
   *out = g_scratch_addr[device];
   return hipSuccess;
 }
+
+// Plan numbers of the matrix-core kernel, after the other plans'.
+int matrix_plan() { return sf::group_plan_count(); }
+int matrix_mixed_plan() { return sf::mixed_plan_count(); }
+constexpr int kMatrixSlots[3] = {4, 16, 64};  // its builds: spots per wavefront
 
 int ppl_index(int ppl) {
   switch (ppl) {
@@ -246,13 +252,27 @@ int spotfit_ctx_create(spotfit_ctx_t** out, int device) {
     }
     c->occ_mixed[pl] = nb > 0 ? nb : 1;
   }
-  // default mixed-size plan (the last): narrow 4x2 lanes x columns for <= 8 px,
-  // lane-owned 4-lane groups of 4 spots for <= 16 px, lane-owned 16-lane groups of
-  // 4 spots for <= 32 px
-  c->mixed_plan = sf::mixed_plan_count() - 1;
+  for (int i = 0; i < 3; ++i) {
+    for (int wide = 0; wide < 2; ++wide) {
+      int nb = 0;
+      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+          &nb, sf::matrix_kernel_symbol(kMatrixSlots[i], wide != 0), 64, 0);
+      if (e != hipSuccess) {
+        delete c;
+        return fail_hip(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
+      }
+      c->occ_matrix[i][wide] = nb > 0 ? nb : 1;
+    }
+  }
+  if (const char* env = std::getenv("SPOTFIT_MATRIX_SLOTS")) {
+    const int v = std::atoi(env);
+    if (v == 4 || v == 16 || v == 64) c->matrix_slots = v;
+  }
+  // default mixed-size plan: the matrix-core kernel
+  c->mixed_plan = matrix_mixed_plan();
   if (const char* env = std::getenv("SPOTFIT_MIXED_PLAN")) {
     const int v = std::atoi(env);
-    if (v >= 0 && v < sf::mixed_plan_count()) {
+    if (v >= 0 && v <= matrix_mixed_plan()) {
       c->mixed_plan = v;
       c->mixed_forced = true;
     }
@@ -268,19 +288,14 @@ int spotfit_ctx_create(spotfit_ctx_t** out, int device) {
     return fail_hip(e, "hipGetSymbolAddress (no-allocation scratch)");
   }
   e = hipMalloc((void**)&c->stats, sizeof(unsigned long long) * kStatsLen);
-  if (e == hipSuccess) e = hipMalloc((void**)&c->queue, 256);
+  if (e == hipSuccess) e = hipMalloc((void**)&c->queue, sizeof(int32_t) * sf::kMatrixCounters * sf::kMatrixCounterWords);
   if (e != hipSuccess) {
     if (c->stats) (void)hipFree(c->stats);
     delete c;
     return fail_hip(e, "hipMalloc (context buffers)");
   }
-  // default plan per size class (measured on MI355X), all lane-owned (taken for
-  // batches large enough, else the narrow plan of the same bits): <= 8 px side:
-  // 4-lane groups of 4 spots, 2 columns per lane; <= 16: 4 columns per lane;
-  // <= 32: 16-lane groups of 4 spots, 2 columns per lane
-  c->plan_for_class[0] = sf::owned_plan_id(4, 2, 4);
-  c->plan_for_class[1] = sf::owned_plan_id(4, 4, 4);
-  c->plan_for_class[2] = sf::owned_plan_id(16, 2, 4);
+  // default plan of every size class: the matrix-core kernel
+  for (int i = 0; i < 3; ++i) c->plan_for_class[i] = matrix_plan();
   if (const char* env = std::getenv("SPOTFIT_GROUP_PLAN")) {
     // tuning override "a,b,c": plan for each size class
     int a = -1, b = -1, d = -1;
@@ -289,8 +304,8 @@ int spotfit_ctx_create(spotfit_ctx_t** out, int device) {
       const int side[3] = {8, 16, 32};
       for (int i = 0; i < 3; ++i) {
         int L = 0, C = 0;
-        sf::group_plan_shape(want[i], &L, &C);
-        if (L * C >= side[i]) {
+        if (want[i] != matrix_plan()) sf::group_plan_shape(want[i], &L, &C);
+        if (want[i] == matrix_plan() || L * C >= side[i]) {
           c->plan_for_class[i] = want[i];
           c->plan_forced[i] = true;
         }
@@ -394,6 +409,26 @@ int64_t owned_min_halves(int plan) {
 // whole batch; measured at 2M spots only).
 constexpr int64_t kOwnedMinSpotsPerLane = 4;
 
+// Batches of uneven sizes up to this many spots are fitted in the order given.
+constexpr int64_t kMatrixUnsorted = 65536;
+
+// Whether a fit with these options runs the matrix-core kernel: both plan hints,
+// unless an override or the autotuner chose another plan.
+bool takes_matrix(const spotfit_ctx_t* ctx, const spotfit_options_t& o) {
+  if (o.precision != SPOTFIT_PREC_FP64) return false;
+  if (o.plan_hint == SPOTFIT_PLAN_LATENCY) return true;
+  if (o.schedule == SPOTFIT_SCHEDULE_MIXED) return ctx->mixed_plan == matrix_mixed_plan();
+  return ctx->plan_for_class[o.max_side <= 8 ? 0 : o.max_side <= 16 ? 1 : 2] == matrix_plan();
+}
+
+// Spots per wavefront (index into kMatrixSlots) for a batch of n spots.
+int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, bool wide) {
+  if (ctx->matrix_slots) return ctx->matrix_slots == 4 ? 0 : ctx->matrix_slots == 16 ? 1 : 2;
+  const int64_t waves = (int64_t)ctx->n_cu * ctx->occ_matrix[0][wide ? 1 : 0];
+  if (n <= 4 * waves) return 0;
+  return n <= 128 * waves ? 1 : 2;
+}
+
 // Enqueue one fit with validated options o and n > 0.  init_out not NULL (with
 // init NULL): the separable double-precision kernels compute the start values
 // themselves and write them there.  Mixed schedule: `classified` is a
@@ -437,7 +472,52 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
   ka.opt.sigma_max_frac = o.sigma_max_frac;
 
   hipError_t e;
-  if (o.precision == SPOTFIT_PREC_FP64 && o.schedule == SPOTFIT_SCHEDULE_MIXED) {
+  if (takes_matrix(ctx, o)) {
+    const bool mixed = o.schedule == SPOTFIT_SCHEDULE_MIXED;
+    if (init_out) {
+      e = sf::launch_start_values(sf::kInitMoments, data, dtype, sizes, offsets, n, o.max_side,
+                                  o.max_pixels, init_out, (hipStream_t)stream);
+      if (e != hipSuccess) return fail_hip(e, "start-value kernel launch");
+      ka.init = init_out;
+      ka.init_out = nullptr;
+    }
+    // a large batch of uneven sizes goes through the sorted class lists, so that
+    // the spots of a pass have one size
+    const bool lists = mixed && n > kMatrixUnsorted && n <= (int64_t)1 << 30;
+    sf::MixedWs ws{};
+    if (lists) {
+      if (!classified && !own_ws && n > ctx->ws_cap) {
+        const int rr = spotfit_ctx_reserve(ctx, n);
+        if (rr != SPOTFIT_OK) return rr;
+      }
+      ws = classified ? *classified
+           : own_ws   ? *own_ws
+                      : sf::MixedWs{ctx->ws, ctx->ws + sf::kMixedHeadWords, ctx->ws_cap, ctx->ws + 8};
+      if (!classified) {
+        e = sf::launch_classify(ka, ws, (hipStream_t)stream);
+        if (e != hipSuccess) return fail_hip(e, "classify launch");
+      }
+    }
+    const bool wide = o.max_side > 16;
+    const int si = matrix_slot_index(ctx, n, wide);
+    const int resident = ctx->n_cu * ctx->occ_matrix[si][wide ? 1 : 0];
+    e = hipSuccess;
+    const int64_t chunk = (int64_t)1 << 30;  // the spot counter is 32-bit
+    for (int64_t c0 = 0; c0 < n && e == hipSuccess; c0 += chunk) {
+      sf::KArgs kc = ka;
+      kc.n = n - c0 < chunk ? n - c0 : chunk;
+      kc.sizes = sizes + c0;
+      kc.offsets = offsets + c0;
+      kc.init = ka.init + 4 * c0;
+      kc.params_out = params_out + 6 * c0;
+      kc.chi2_out = chi2_out + c0;
+      kc.iters_out = iters_out + c0;
+      kc.status_out = status_out + c0;
+      kc.evals_out = evals_out ? evals_out + 2 * c0 : nullptr;
+      e = sf::launch_matrix_kernel(kMatrixSlots[si], wide, kc, lists ? &ws : nullptr, resident,
+                                   (hipStream_t)stream);
+    }
+  } else if (o.precision == SPOTFIT_PREC_FP64 && o.schedule == SPOTFIT_SCHEDULE_MIXED) {
     if (!classified && !own_ws && n > ctx->ws_cap) {
       const int rr = spotfit_ctx_reserve(ctx, n);
       if (rr != SPOTFIT_OK) return rr;
@@ -548,7 +628,7 @@ int launch_raw(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
                const int64_t* offsets, int64_t n, const spotfit_options_t& o, float* init_out,
                float* params_out, float* chi2_out, int32_t* iters_out, int32_t* status_out,
                int32_t* evals_out, void* stream, const sf::MixedWs* own_ws = nullptr) {
-  if (o.precision == SPOTFIT_PREC_FP64 && !takes_owned(ctx, n, o))
+  if (takes_matrix(ctx, o) || (o.precision == SPOTFIT_PREC_FP64 && !takes_owned(ctx, n, o)))
     return launch_fit(ctx, data, dtype, sizes, offsets, nullptr, n, o, params_out, chi2_out,
                       iters_out, status_out, evals_out, stream, init_out, nullptr, own_ws);
   const hipError_t e = sf::launch_start_values(sf::kInitMoments, data, dtype, sizes, offsets, n,
@@ -714,8 +794,10 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   int cand[16];
   int nc = 0;
   if (mixed) {
+    cand[nc++] = matrix_mixed_plan();
     for (int p = 0; p < sf::mixed_plan_count() && nc < 16; ++p) cand[nc++] = p;
   } else {
+    cand[nc++] = matrix_plan();
     for (int p = 0; p < sf::group_plan_count() && nc < 16; ++p) {
       int L = 0, C = 0;
       sf::group_plan_shape(p, &L, &C);

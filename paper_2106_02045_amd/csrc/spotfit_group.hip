@@ -896,7 +896,7 @@ const void* mixed_kernel_symbol(int plan) {
   return nullptr;
 }
 
-hipError_t launch_mixed(int plan, const KArgs& ka, const MixedWs& ws, int grid, hipStream_t st) {
+hipError_t launch_classify(const KArgs& ka, const MixedWs& ws, hipStream_t st) {
   hipError_t e;
   if (!ws.sort) return hipErrorInvalidValue;
   if (ka.n <= 65536) {
@@ -922,8 +922,12 @@ hipError_t launch_mixed(int plan, const KArgs& ka, const MixedWs& ws, int grid, 
       e = hipGetLastError();
     }
   }
-  if (e != hipSuccess) return e;
-  return launch_mixed_fit(plan, ka, ws, grid, st);
+  return e;
+}
+
+hipError_t launch_mixed(int plan, const KArgs& ka, const MixedWs& ws, int grid, hipStream_t st) {
+  const hipError_t e = launch_classify(ka, ws, st);
+  return e == hipSuccess ? launch_mixed_fit(plan, ka, ws, grid, st) : e;
 }
 
 hipError_t launch_mixed_fit(int plan, const KArgs& ka, const MixedWs& ws, int grid, hipStream_t st) {

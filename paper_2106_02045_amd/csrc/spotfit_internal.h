@@ -135,6 +135,20 @@ int mixed_plan_narrow(int plan);
 hipError_t launch_narrow_mixed_fit(int plan, const KArgs& ka, const MixedWs& ws, int grid,
                                    hipStream_t st);
 
+// The matrix-core kernel (spots up to 32 px; wide: sides above 16 px may occur).
+// `slots` spots per wavefront: 4, 16 or 64, the same bits for each.  `resident`:
+// wavefronts to launch at most; a batch of more spots than they hold draws the
+// rest from kMatrixCounters counters, one cache line each, at ka.queue (cleared
+// here).  ws: class lists to go through, largest class first, or null: spots in
+// order.  ka.n <= 2^30; reads ka.init.
+constexpr int kMatrixCounters = 32;
+constexpr int kMatrixCounterWords = 32;  // from one counter to the next
+const void* matrix_kernel_symbol(int slots, bool wide);
+hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const MixedWs* ws, int resident,
+                                hipStream_t st);
+// The classify pass of a mixed-size launch alone.
+hipError_t launch_classify(const KArgs& ka, const MixedWs& ws, hipStream_t st);
+
 // Start values from the pixels for spots with sides up to max_side: float[n][4]
 // into out.  kInitMoments: centroid / second moments; kInitPeak: the paper's
 // recipe (brightest pixel of the 3 x 3 moving average, sigma = sqrt(M / pi)).
