@@ -386,11 +386,18 @@ __device__ __forceinline__ Amplitudes slot_amplitudes(const Shared<NS>& L, int s
 // at their candidates, four a pass (Eqs. 2, 5-7, 10), into L.tot.  Every slot
 // has the shape of geo0, with TB columns per lane group and TB row tiles.  Float
 // data: with chi^2 summed over the pixels.
+//
+// The pixels of a pass stay in registers, and the next pass's take their places
+// as they are used; of floats above 16 px, whose 40 to 64 registers would push
+// the owners' state out of the registers, kRows row tiles are in flight instead,
+// read once for the products and once for the residuals (200,000 of 17x17:
+// 826 us held, 683 read twice).
 template <int NS, int DT, int TB>
 __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L, int cnt, int cnt_new,
                                                  uint32_t geo0) {
   constexpr int CH = (TB + 3) / 4;
-  constexpr bool kFloat = DT != SPOTFIT_U16;
+  constexpr bool kFloat = DT != SPOTFIT_U16, kRing = kFloat && CH > 1;
+  constexpr int kRows = kRing ? 4 : TB;
   // opaque: a lane's constants are formed once a step here, not held in
   // registers over the rest of it
   int lane = __lane_id();
@@ -398,7 +405,7 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   const Lane ln(lane);
   Window<CH, DT> win;
   win.set(geo0, ln.v, ln.k);
-  Raw<DT> px[TB][CH];
+  Raw<DT> px[kRows][CH];
   auto slot_at = [&](int p) { return L.order[p + ln.blk < cnt ? p + ln.blk : cnt - 1]; };
   const char* base[CH];
   auto aim = [&](int sl) {  // at the first rows of a slot's windows
@@ -407,27 +414,79 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
     for (int q = 0; q < CH; ++q) base[q] = p + win.start[q] * Raw<DT>::kSize;
   };
   uint32_t rb;
-  auto load_row = [&](auto ai) {
-    constexpr int at = decltype(ai)::value;
+  auto rewind = [&] {
+    rb = win.row;
+    if constexpr (CH > 1) asm volatile("" : "+v"(rb));  // its rows' offsets do not fit the registers
+  };
+  auto load_next = [&](Raw<DT> (&to)[CH]) {
 #pragma unroll
-    for (int q = 0; q < CH; ++q) px[at][q].load(base[q] + (rb < win.last[q] ? rb : win.last[q]));
+    for (int q = 0; q < CH; ++q) to[q].load(base[q] + (rb < win.last[q] ? rb : win.last[q]));
     rb += win.step;
   };
+  // the last row tile holds the last row: windows cut off there come back
+  auto put_back = [&](auto ai, Raw<DT> (&row)[CH]) {
+    constexpr int at = decltype(ai)::value;
+    if constexpr (at == TB - 1) {
+#pragma unroll
+      for (int q = 0; q < CH; ++q) row[q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
+    }
+  };
+  // after item i of a ring pass (TB row tiles for the products, then for the
+  // residuals): the item that takes its place
+  auto refill = [&](auto ii) {
+    constexpr int i = decltype(ii)::value + kRows;
+    if constexpr (i < 2 * TB) {
+      if constexpr (i == TB) rewind();
+      load_next(px[i % kRows]);
+    }
+  };
+  auto add_row = [&](auto ai, const Raw<DT> (&row)[CH], double& sg, double& sgg) {
+    constexpr int at = decltype(ai)::value;
+    const bool rowin = at < TB - 1 || 4 * at + ln.v < win.h;
+    unrolled<TB>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      const double g = row[t / 4].template get<t % 4>();
+      // a group owns at least T - 3 columns
+      const double gm = rowin && (t < TB - 3 || t % 4 < win.own[t / 4]) ? g : 0.0;
+      sg += gm;
+      sgg = __builtin_fma(gm, gm, sgg);
+    });
+    __builtin_amdgcn_sched_barrier(0);
+  };
   int slot = slot_at(0);
-  aim(slot);
-  rb = win.row;
-  unrolled<TB>(load_row);
+  if constexpr (!kRing) {
+    aim(slot);
+    rb = win.row;
+    unrolled<TB>([&](auto ai) { load_next(px[decltype(ai)::value]); });
+  }
 
 #pragma unroll 1
   for (int p = 0; p < cnt; p += 4) {
     const double x = L.x[slot], y = L.y[slot], hx = L.hx[slot], hy = L.hy[slot];
     const int cslot = slot;
+    if constexpr (kRing) {
+      aim(slot);
+      if (p < cnt_new) {
+        double sg = 0.0, sgg = 0.0;
+        rewind();
+        unrolled<TB>([&](auto ai) {
+          Raw<DT> row[CH];
+          load_next(row);
+          put_back(ai, row);
+          add_row(ai, row, sg, sgg);
+        });
+        put_pixel_sums(ln, L, cslot, p + ln.blk < cnt_new, sg, sgg);
+      }
+      rewind();
+      unrolled<kRows>([&](auto ai) { load_next(px[decltype(ai)::value]); });
+    }
     // the next pass (or this one's last slot again): its rows are loaded as this
     // pass's are used
     slot = slot_at(p + 4);
-    aim(slot);
-    rb = win.row;
-    if constexpr (CH > 1) asm volatile("" : "+v"(rb));  // its rows' offsets do not fit the registers
+    if constexpr (!kRing) {
+      aim(slot);
+      rewind();
+    }
     double exq[CH], eyq[CH], V[TB], E[TB];
     double R = 0.0, GX = 0.0, GY = 0.0;
     unrolled<CH>([&](auto qi) {
@@ -445,64 +504,57 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
       if constexpr (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_sched_barrier(0);
-    // the last row tile holds the last row: windows cut off there come back
+    if constexpr (!kRing) {
+      put_back(std::integral_constant<int, TB - 1>{}, px[TB - 1]);
+      if (p < cnt_new) {
+        double sg = 0.0, sgg = 0.0;
+        unrolled<TB>([&](auto ai) {
+          constexpr int at = decltype(ai)::value;
+          Raw<DT> row[CH];
 #pragma unroll
-    for (int q = 0; q < CH; ++q)
-      px[TB - 1][q].shift(4 * (TB - 1) + ln.v >= win.h - 1 ? win.over[q] : 0);
-    if (p < cnt_new) {
-      double sg = 0.0, sgg = 0.0;
-      unrolled<TB>([&](auto ai) {
-        constexpr int at = decltype(ai)::value;
-        const bool rowin = at < TB - 1 || 4 * at + ln.v < win.h;
-        Raw<DT> row[CH];
-#pragma unroll
-        for (int q = 0; q < CH; ++q) row[q] = px[at][q].fresh();
-        unrolled<TB>([&](auto bi) {
-          constexpr int t = decltype(bi)::value;
-          const double g = row[t / 4].template get<t % 4>();
-          // a group owns at least T - 3 columns
-          const double gm = rowin && (t < TB - 3 || t % 4 < win.own[t / 4]) ? g : 0.0;
-          sg += gm;
-          sgg = __builtin_fma(gm, gm, sgg);
+          for (int q = 0; q < CH; ++q) row[q] = px[at][q].fresh();
+          add_row(ai, row, sg, sgg);
         });
-        __builtin_amdgcn_sched_barrier(0);
-      });
-      put_pixel_sums(ln, L, cslot, p + ln.blk < cnt_new, sg, sgg);
+        put_pixel_sums(ln, L, cslot, p + ln.blk < cnt_new, sg, sgg);
+      }
     }
     unrolled<TB>([&](auto ai) {
       constexpr int at = decltype(ai)::value;
+      if constexpr (kRing) put_back(ai, px[at % kRows]);
       double S = 0.0;
       unrolled<TB>([&](auto bi) {
         constexpr int t = decltype(bi)::value;
-        S = mfma4(px[at][t / 4].template get<t % 4>(), V[t], S);
+        S = mfma4(px[at % kRows][t / 4].template get<t % 4>(), V[t], S);
       });
       R = mfma4(E[at], S, R);
-      if constexpr (!kFloat) load_row(ai);
+      if constexpr (kRing) refill(ai);
+      else if constexpr (!kFloat) load_next(px[at]);
       __builtin_amdgcn_sched_barrier(0);  // bounds the tiles in flight (registers)
     });
     put_totals(ln, L, cslot, R, GX, GY);
     if constexpr (kFloat) {
       wave_lds_sync();
       const Amplitudes am = slot_amplitudes(L, cslot, win.w, win.h);
-      double c2s = 0.0;
-      unrolled<CH>([&](auto qi) {
-        constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
-        double aex[4], cs[4];
-        unrolled<B>([&](auto bi) {
-          constexpr int t = decltype(bi)::value;
-          aex[t] = am.a * lg::gbcast<4, t>(exq[q]);
-          cs[t] = 0.0;
+      double aex[CH][4], cs[CH][4], c2s = 0.0;
+      unrolled<TB>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        aex[t / 4][t % 4] = am.a * lg::gbcast<4, t % 4>(exq[t / 4]);
+        cs[t / 4][t % 4] = 0.0;
+      });
+      unrolled<TB>([&](auto ai) {
+        constexpr int at = decltype(ai)::value, i = kRing ? TB + at : at;
+        if constexpr (kRing) put_back(ai, px[i % kRows]);
+        unrolled<CH>([&](auto qi) {
+          constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
+          residual_row<at, B>(ln, px[i % kRows][q].fresh(), aex[q], eyq[at / 4], am.b, win.h, cs[q]);
         });
-        unrolled<TB>([&](auto ai) {
-          constexpr int at = decltype(ai)::value;
-          residual_row<at, B>(ln, px[at][q].fresh(), aex, eyq[at / 4], am.b, win.h, cs);
-          if constexpr (q == CH - 1) load_row(ai);
-          __builtin_amdgcn_sched_barrier(0);
-        });
-        unrolled<B>([&](auto bi) {
-          constexpr int t = decltype(bi)::value;
-          c2s += t < win.own[q] ? cs[t] : 0.0;
-        });
+        if constexpr (kRing) refill(std::integral_constant<int, i>{});
+        else load_next(px[at]);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      unrolled<TB>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        c2s += t % 4 < win.own[t / 4] ? cs[t / 4][t % 4] : 0.0;
       });
       c2s = block_sum(c2s);
       if (ln.v == 0 && ln.k == 0) L.tot[kChi][cslot] = c2s;
@@ -690,13 +742,129 @@ __device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, in
   }
 }
 
+// A wavefront of 4 slots: block b evaluates slot b, whose candidate and pixels
+// (shifted into place) its lanes hold in registers from step to step, so a step
+// neither reads memory nor waits for it.  A lone wavefront per SIMD is bound by
+// that chain of latencies: 32 markers of 13x13 px 38.6 us a replayed frame (40.6
+// with the pixels read at each step), 1,024 of 11x11 18.0 (19.5), 640 raw spots
+// of 9..21 px 41.0 (47.3).
+struct Candidate {
+  double x, y, hx, hy;
+};
+
+// One pass over the 4 slots at their candidates, into L.tot.  load: read the
+// pixels of every slot first, at `off`; some slot (fresh) is then a new spot.
+// Every slot has at most TB columns per lane group and TB row tiles; the tiles
+// that a smaller one does not have add zeros to its sums.
+template <int CH, int DT, int TB>
+__device__ __forceinline__ void evaluate_blocks(const void* data, Shared<4>& L, Raw<DT> (&px)[4 * CH][CH],
+                                                const Candidate& c, int64_t off, uint32_t geo, bool load,
+                                                bool fresh) {
+  constexpr int CQ = (TB + 3) / 4;
+  int lane = __lane_id();
+  asm volatile("" : "+v"(lane));
+  const Lane ln(lane);
+  Window<CQ, DT> win;
+  win.set(geo, ln.v, ln.k);
+  if (load) {
+    const char* base = static_cast<const char*>(data) + off * Raw<DT>::kSize;
+    uint32_t rb = win.row;
+    unrolled<TB>([&](auto ai) {
+      constexpr int at = decltype(ai)::value;
+#pragma unroll
+      for (int q = 0; q < CQ; ++q)
+        px[at][q].load(base + win.start[q] * Raw<DT>::kSize + (rb < win.last[q] ? rb : win.last[q]));
+      rb += win.step;
+    });
+  }
+  double exq[CQ], eyq[CQ], V[TB], E[TB];
+  double R = 0.0, GX = 0.0, GY = 0.0;
+  unrolled<CQ>([&](auto qi) {
+    constexpr int q = decltype(qi)::value;
+    factors<q>(ln, win, c.x, c.y, c.hx, c.hy, exq[q], eyq[q]);
+  });
+  const double dy0 = double(ln.k) - c.y;
+  unrolled<TB>([&](auto ti) {
+    constexpr int t = decltype(ti)::value;
+    const double dx = (double(win.start[t / 4]) - c.x) + double(t % 4);
+    V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
+    GX = mfma4(V[t], V[t], GX);
+    E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
+    GY = mfma4(E[t], E[t], GY);
+  });
+  if (load) {  // the windows cut off by a spot's end
+    unrolled<TB>([&](auto ai) {
+      constexpr int at = decltype(ai)::value;
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) px[at][q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
+    });
+    double sg = 0.0, sgg = 0.0;
+    unrolled<TB>([&](auto ai) {
+      constexpr int at = decltype(ai)::value;
+      const bool rowin = 4 * at + ln.v < win.h;
+      Raw<DT> row[CQ];
+#pragma unroll
+      for (int q = 0; q < CQ; ++q) row[q] = px[at][q].fresh();
+      unrolled<TB>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        const double g = row[t / 4].template get<t % 4>();
+        const double gm = rowin && t % 4 < win.own[t / 4] ? g : 0.0;
+        sg += gm;
+        sgg = __builtin_fma(gm, gm, sgg);
+      });
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    put_pixel_sums(ln, L, ln.blk, fresh, sg, sgg);
+  }
+  unrolled<TB>([&](auto ai) {
+    constexpr int at = decltype(ai)::value;
+    Raw<DT> row[CQ];
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) row[q] = px[at][q].fresh();
+    double S = 0.0;
+    unrolled<TB>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      S = mfma4(row[t / 4].template get<t % 4>(), V[t], S);
+    });
+    R = mfma4(E[at], S, R);
+    if constexpr (at % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+  });
+  put_totals(ln, L, ln.blk, R, GX, GY);
+  if constexpr (DT != SPOTFIT_U16) {
+    wave_lds_sync();
+    const Amplitudes am = slot_amplitudes(L, ln.blk, win.w, win.h);
+    double c2s = 0.0;
+    unrolled<CQ>([&](auto qi) {
+      constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
+      double aex[4], cs[4];
+      unrolled<B>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        aex[t] = am.a * lg::gbcast<4, t>(exq[q]);
+        cs[t] = 0.0;
+      });
+      unrolled<TB>([&](auto ai) {
+        constexpr int at = decltype(ai)::value;
+        residual_row<at, B>(ln, px[at][q].fresh(), aex, eyq[at / 4], am.b, win.h, cs);
+        __builtin_amdgcn_sched_barrier(0);
+      });
+      unrolled<B>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        c2s += t < win.own[q] ? cs[t] : 0.0;
+      });
+    });
+    c2s = block_sum(c2s);
+    if (ln.v == 0 && ln.k == 0) L.tot[kChi][ln.blk] = c2s;
+  }
+}
+
 // The kernel's arguments, read anew where they are used (scalar loads from the
 // argument segment) instead of held in scalar registers over the whole fit,
 // where they do not fit.
 typedef const __attribute__((address_space(4))) KArgs* ArgPtr;
+template <bool ANEW = true>
 __device__ __forceinline__ ArgPtr args() {
   ArgPtr p = (ArgPtr)__builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
+  if constexpr (ANEW) asm volatile("" : "+s"(p));
   return p;
 }
 
@@ -812,7 +980,6 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
   constexpr int HM = 16 * CH;
   constexpr bool kKeepA = Shared<NS>::kKeepA;
   const int lane = __lane_id();
-  const void* data = args()->data;
   // Slots and their owners: lane l < NS owns slot l; of 4 slots, all 16 lanes of
   // a block own its slot, each taking the same steps, so that they can share out
   // the normal equations.  lead: the owner that speaks for its slot.
@@ -826,13 +993,37 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
   };
 
-  // ---- the owner's state (its candidate is in L) ----
+  // a wavefront of 4 slots is there for short steps: it does not wait for its
+  // arguments again
+  const auto args = [] { return mtx::args<!kBlocks>(); };
+  const void* data = args()->data;
+
+  // ---- the owner's state (its candidate is in L; of 4 slots: in registers) ----
   int32_t s = -1;
+  double pc[4] = {0.0, 0.0, 1.0, 1.0};  // candidate
+  Candidate cand{};
+  int64_t off = 0;
+  uint32_t geo = 0;
+  Raw<DT> px[4 * CH][CH];
   int k = 0, it = 0, mode = kNew, n_grad = 0, n_trial = 0;
   bool small = false;
   double best[4] = {0.0, 0.0, 0.0, 0.0};  // point at the start of the iteration
   double chi_best = 0.0, a_best = 0.0, b_best = 0.0, chib_err = 0.0;
 
+  // The candidate pc, for the next evaluation.
+  auto publish = [&](bool fresh) {
+    cand = Candidate{pc[0], pc[1], -0.5 * rcp_nr(pc[2] * pc[2]), -0.5 * rcp_nr(pc[3] * pc[3])};
+    if constexpr (!kBlocks) {
+      L.x[own] = cand.x;
+      L.y[own] = cand.y;
+      L.sx[own] = pc[2];
+      L.sy[own] = pc[3];
+      L.hx[own] = cand.hx;
+      L.hy[own] = cand.hy;
+      L.geo[own] = geo;
+      if (fresh) L.off[own] = off;
+    }
+  };
   // Taking a spot, in two steps so that its loads are in flight over other work:
   // look up queue position pos, then start the spot (an unusable one ends here).
   struct Next {
@@ -870,15 +1061,13 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
       s = -1;
       return;
     }
-    const double sx = nin.z, sy = ell ? nin.w : nin.z;
-    L.x[own] = nin.x;
-    L.y[own] = nin.y;
-    L.sx[own] = sx;
-    L.sy[own] = sy;
-    L.hx[own] = -0.5 * rcp_nr(sx * sx);
-    L.hy[own] = -0.5 * rcp_nr(sy * sy);
-    L.off[own] = noff;
-    L.geo[own] = uint32_t(nsh.w) | uint32_t(nsh.h) << 8 | kGeoNew | (ell ? kGeoEll : 0u);
+    pc[0] = nin.x;
+    pc[1] = nin.y;
+    pc[2] = nin.z;
+    pc[3] = ell ? nin.w : nin.z;
+    off = noff;
+    geo = uint32_t(nsh.w) | uint32_t(nsh.h) << 8 | kGeoNew | (ell ? kGeoEll : 0u);
+    publish(true);
     k = ka->opt.lambda0_exp10;
     it = 0;
     mode = kNew;
@@ -907,45 +1096,65 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
     const uint64_t m_act = __builtin_amdgcn_ballot_w64(act && lead);
     const uint64_t m_new = __builtin_amdgcn_ballot_w64(fresh && lead);
     const int cnt = __builtin_popcountll(m_act);
-    if (act && lead) {
-      const int rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
-      L.order[rank] = own;
+    if constexpr (!kBlocks) {
+      if (act) {
+        const int rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
+        L.order[rank] = own;
+      }
+      wave_lds_sync();
+      geo = L.geo[owner ? own : 0];
     }
-    wave_lds_sync();
-    const uint32_t geo = L.geo[owner ? own : 0];
     const int w = geo & 0xff, h = (geo >> 8) & 0xff;
     if (cnt > 0) {
       const int cnt_new = __builtin_popcountll(m_new);
-      const uint32_t geo0 =
-          (uint32_t)__builtin_amdgcn_readlane((int)geo, __builtin_ctzll(m_act)) & 0xffffu;
+      const int lead0 = __builtin_ctzll(m_act);
+      const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0) & 0xffffu;
       const int T = ((geo0 & 0xff) + 3) >> 2;
-      const bool uni = T == (int)((geo0 >> 8) + 3) >> 2 &&
-                       __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
-      bool done = false;
-      unrolled<4 * CH - 1>([&](auto ti) {
-        constexpr int TB = decltype(ti)::value + 2;
-        if (uni && T == TB) {
-          evaluate_uniform<NS, DT, TB>(data, L, cnt, cnt_new, geo0);
-          done = true;
-        }
-      });
-      if (!done) evaluate_any<NS, CH, DT>(data, L, cnt, cnt_new);
+      if constexpr (kBlocks) {
+        // a block without a spot goes along on the first one's pixels
+        const int2 o = __builtin_bit_cast(int2, off);
+        const int2 o0 = make_int2(__builtin_amdgcn_readlane(o.x, lead0), __builtin_amdgcn_readlane(o.y, lead0));
+        const int64_t at = act ? off : __builtin_bit_cast(int64_t, o0);
+        const uint32_t shape = act ? geo : geo0;
+        // tiles for the largest side of the four (at least 2)
+        const int side = (shape & 0xff) > (shape >> 8 & 0xff) ? shape & 0xff : shape >> 8 & 0xff;
+        const int tiles = max_over_blocks((side + 3) >> 2);
+        unrolled<4 * CH - 1>([&](auto ti) {
+          constexpr int TB = decltype(ti)::value + 2;
+          if (tiles == TB || (TB == 2 && tiles < 2))
+            evaluate_blocks<CH, DT, TB>(data, L, px, cand, at, shape, cnt_new != 0, fresh);
+        });
+      } else {
+        const bool uni = T == (int)((geo0 >> 8) + 3) >> 2 &&
+                         __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
+        bool done = false;
+        unrolled<4 * CH - 1>([&](auto ti) {
+          constexpr int TB = decltype(ti)::value + 2;
+          if (uni && T == TB) {
+            evaluate_uniform<NS, DT, TB>(data, L, cnt, cnt_new, geo0);
+            done = true;
+          }
+        });
+        if (!done) evaluate_any<NS, CH, DT>(data, L, cnt, cnt_new);
+      }
       wave_lds_sync();
     }
 
     // ================= the owner's scalar steps =================
     const bool sym = !(geo & kGeoEll);
     const double Nn = double(w * h);
-    double pc[4] = {0.0, 0.0, 0.0, 0.0}, A[10], bv[4];
+    double A[10], bv[4];
     double Sx, Sxx, Sy, Syy, FG, Gs, chi = 0.0, chi_err = 0.0;
     Amplitudes am{};
     bool do_grad = false, do_solve = false, near_self = false, near_best = false;
     if (act) {
       const ArgPtr ka = args();
-      pc[0] = L.x[own];
-      pc[1] = L.y[own];
-      pc[2] = L.sx[own];
-      pc[3] = L.sy[own];
+      if constexpr (!kBlocks) {
+        pc[0] = L.x[own];
+        pc[1] = L.y[own];
+        pc[2] = L.sx[own];
+        pc[3] = L.sy[own];
+      }
       Sx = L.tot[kSx][own];
       Sxx = L.tot[kSxx][own];
       Sy = L.tot[kSy][own];
@@ -990,6 +1199,13 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
               L.y[own] = best[1];
               L.hx[own] = -0.5 * rcp_nr(best[2] * best[2]);
               L.hy[own] = -0.5 * rcp_nr(best[3] * best[3]);
+            } else if constexpr (kBlocks) {
+              L.x[own] = cand.x;
+              L.y[own] = cand.y;
+              L.hx[own] = cand.hx;
+              L.hy[own] = cand.hy;
+              L.off[own] = off;
+              L.geo[own] = geo;
             }
           }
           wave_lds_sync();
@@ -1184,15 +1400,9 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
                 fabs(d[1]) < rel * fabs(best[1] - 0.5 * double(h - 1)) &&
                 fabs(d[2]) < rel * fabs(best[2]) && (sym || fabs(d[3]) < rel * fabs(best[3]));
       }
-      // the candidate of the next evaluation
       if (act) {
-      L.x[own] = pc[0];
-      L.y[own] = pc[1];
-      L.sx[own] = pc[2];
-      L.sy[own] = pc[3];
-      L.hx[own] = -0.5 * rcp_nr(pc[2] * pc[2]);
-      L.hy[own] = -0.5 * rcp_nr(pc[3] * pc[3]);
-      L.geo[own] = geo & ~kGeoNew;
+        geo &= ~kGeoNew;
+        publish(false);
       }
     }
     if (taking && s >= 0) begin(nx);
