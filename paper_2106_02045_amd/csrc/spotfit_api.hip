@@ -31,8 +31,8 @@ struct spotfit_ctx {
   int mixed_plan;
   bool mixed_forced;  // set by the SPOTFIT_MIXED_PLAN override
   int occ_mixed[8];
-  int occ_matrix[3][2];  // matrix-core kernel: by spots per wavefront (4, 16, 64) and width
-  int matrix_slots;      // SPOTFIT_MATRIX_SLOTS override: 4, 16 or 64; else 0
+  int occ_matrix[4][2][2];  // matrix-core kernel: by spots per wavefront, width and pixel type
+  int matrix_slots;      // SPOTFIT_MATRIX_SLOTS override: one of kMatrixSlots; else 0
   int32_t* ws;      // counters[8] then 3 lists of ws_cap spot indices
   int64_t ws_cap;
   unsigned long long* stats;  // device histogram buffer of spotfit_get_stats
@@ -92,7 +92,8 @@ hipError_t scratch_address(int device, int32_t** out) {
 // Plan numbers of the matrix-core kernel, after the other plans'.
 int matrix_plan() { return sf::group_plan_count(); }
 int matrix_mixed_plan() { return sf::mixed_plan_count(); }
-constexpr int kMatrixSlots[3] = {4, 16, 64};  // its builds: spots per wavefront
+constexpr int kMatrixBuilds = 4;
+constexpr int kMatrixSlots[kMatrixBuilds] = {4, 16, 32, 64};  // its builds: spots per wavefront
 
 int ppl_index(int ppl) {
   switch (ppl) {
@@ -252,21 +253,22 @@ int spotfit_ctx_create(spotfit_ctx_t** out, int device) {
     }
     c->occ_mixed[pl] = nb > 0 ? nb : 1;
   }
-  for (int i = 0; i < 3; ++i) {
-    for (int wide = 0; wide < 2; ++wide) {
-      int nb = 0;
-      e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &nb, sf::matrix_kernel_symbol(kMatrixSlots[i], wide != 0), 64, 0);
-      if (e != hipSuccess) {
-        delete c;
-        return fail_hip(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
-      }
-      c->occ_matrix[i][wide] = nb > 0 ? nb : 1;
+  for (int i = 0; i < 4 * kMatrixBuilds; ++i) {
+    const int slots = i >> 2, wide = (i >> 1) & 1, f32 = i & 1;
+    int nb = 0;
+    e = hipOccupancyMaxActiveBlocksPerMultiprocessor(
+        &nb, sf::matrix_kernel_symbol(kMatrixSlots[slots], wide != 0, f32 ? SPOTFIT_F32 : SPOTFIT_U16),
+        64, 0);
+    if (e != hipSuccess) {
+      delete c;
+      return fail_hip(e, "hipOccupancyMaxActiveBlocksPerMultiprocessor");
     }
+    c->occ_matrix[slots][wide][f32] = nb > 0 ? nb : 1;
   }
   if (const char* env = std::getenv("SPOTFIT_MATRIX_SLOTS")) {
     const int v = std::atoi(env);
-    if (v == 4 || v == 16 || v == 64) c->matrix_slots = v;
+    for (int i = 0; i < kMatrixBuilds; ++i)
+      if (v == kMatrixSlots[i]) c->matrix_slots = v;
   }
   // default mixed-size plan: the matrix-core kernel
   c->mixed_plan = matrix_mixed_plan();
@@ -409,8 +411,11 @@ int64_t owned_min_halves(int plan) {
 // whole batch; measured at 2M spots only).
 constexpr int64_t kOwnedMinSpotsPerLane = 4;
 
-// Batches of uneven sizes up to this many spots are fitted in the order given.
-constexpr int64_t kMatrixUnsorted = 65536;
+// Batches of uneven sizes up to this many spots are fitted in the order given:
+// a wavefront goes over its own slots by size, and the sort of the whole batch
+// costs more than it saves (7..32 px, in order / sorted: 130,000 spots 320 us /
+// 395, 200,000 486 / 503; 400,000 970 / 959, 2M 3723 / 3185).
+constexpr int64_t kMatrixUnsorted = 262144;
 
 // Whether a fit with these options runs the matrix-core kernel: both plan hints,
 // unless an override or the autotuner chose another plan.
@@ -421,12 +426,34 @@ bool takes_matrix(const spotfit_ctx_t* ctx, const spotfit_options_t& o) {
   return ctx->plan_for_class[o.max_side <= 8 ? 0 : o.max_side <= 16 ? 1 : 2] == matrix_plan();
 }
 
-// Spots per wavefront (index into kMatrixSlots) for a batch of n spots.
-int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, bool wide) {
-  if (ctx->matrix_slots) return ctx->matrix_slots == 4 ? 0 : ctx->matrix_slots == 16 ? 1 : 2;
-  const int64_t waves = (int64_t)ctx->n_cu * ctx->occ_matrix[0][wide ? 1 : 0];
-  if (n <= 4 * waves) return 0;
-  return n <= 128 * waves ? 1 : 2;
+// Wavefronts of the matrix-core kernel that the device holds at once.
+int64_t matrix_resident(const spotfit_ctx_t* ctx, int slots_index, int32_t dtype, int32_t max_side) {
+  return (int64_t)ctx->n_cu * ctx->occ_matrix[slots_index][max_side > 16][dtype == SPOTFIT_F32];
+}
+
+// Spots per wavefront (index into kMatrixSlots) for a batch of n spots.  With few
+// spots a launch takes as long as a spot's steps, and a step is the shorter the
+// fewer spots share it; with many it is the work per spot that counts, which
+// falls with the spots that share the scalar part of a step.  In between, the
+// fewest with which every spot is in flight at once are the fastest, within a
+// few percent.  Measured, 16-bit pixels, us with 4 / 16 / 32 / 64 spots:
+//   9 px     12,000: 34 / 35 / 43 / 64    48,000: 115 / 58 / 60 / 66    100,000: 222 / 124 / 108 / 94
+//   15 px    12,000: 43 / 47 / 58 / 86    65,000: 176 / 99 / 88 / 98    100,000: 245 / 161 / 136 / 131
+//   21 px     8,000: 54 / 67 / 94 / 145   32,000: 149 / 98 / 97 / 149    65,000: 274 / 198 / 147 / 153
+//   32 px     8,000: 71 / 94 / 134 / 217  65,000: 367 / 267 / 202 / 224 100,000: 534 / 379 / 343 / 351
+//   7..32 px  8,000: 54 / 80 / 115 / 190  65,000: 321 / 249 / 188 / 211 130,000: 600 / 414 / 387 / 320
+// Wide floats, whose products wait longer for their pixels, keep 4 spots a
+// little further (17 px, 12,000: 73 / 97; 16,000: 91 / 98).
+int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, int32_t dtype, const spotfit_options_t& o) {
+  int64_t most[kMatrixBuilds - 1];
+  for (int i = 0; i < kMatrixBuilds - 1; ++i)
+    most[i] = kMatrixSlots[i] * matrix_resident(ctx, i, dtype, o.max_side);
+  if (dtype == SPOTFIT_F32 && o.max_side > 16) most[0] = most[0] * 3 / 2;
+  for (int i = 0; i < kMatrixBuilds; ++i) {
+    if (ctx->matrix_slots ? ctx->matrix_slots == kMatrixSlots[i] : i == kMatrixBuilds - 1 || n <= most[i])
+      return i;
+  }
+  return kMatrixBuilds - 1;
 }
 
 // Enqueue one fit with validated options o and n > 0.  init_out not NULL (with
@@ -482,7 +509,7 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
       ka.init_out = nullptr;
     }
     // a large batch of uneven sizes goes through the sorted class lists, so that
-    // the spots of a pass have one size
+    // the spots of a wavefront are about as large as each other
     const bool lists = mixed && n > kMatrixUnsorted && n <= (int64_t)1 << 30;
     sf::MixedWs ws{};
     if (lists) {
@@ -499,8 +526,8 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
       }
     }
     const bool wide = o.max_side > 16;
-    const int si = matrix_slot_index(ctx, n, wide);
-    const int resident = ctx->n_cu * ctx->occ_matrix[si][wide ? 1 : 0];
+    const int si = matrix_slot_index(ctx, n, dtype, o);
+    const int resident = (int)matrix_resident(ctx, si, dtype, o.max_side);
     e = hipSuccess;
     const int64_t chunk = (int64_t)1 << 30;  // the spot counter is 32-bit
     for (int64_t c0 = 0; c0 < n && e == hipSuccess; c0 += chunk) {

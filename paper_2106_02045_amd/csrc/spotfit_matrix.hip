@@ -24,8 +24,10 @@
 // in every launch of this kernel.
 //
 // A wavefront holds NS spots, one owned by each of its first NS lanes: a step
-// evaluates all of them in passes of four (new spots first, so that the sums of
-// g and g^2 are formed in few passes), then every owner takes its spot's scalar
+// evaluates all of them in passes of four (spots of one shape: new ones first, so
+// that the sums of g and g^2 are formed in few passes, and the next pass's pixels
+// are loaded as this one's are used; spots of any shapes: by size, so that few
+// passes go over the tiles of a large one), then every owner takes its spot's scalar
 // steps (Eqs. 6, 8, the normal equations, the damped solve, the decisions of the
 // Fit2DGaussian loop) from the totals in LDS.  NS is the launch's trade between
 // the length of a step and the lanes that share its scalar part: 4 slots (every
@@ -40,10 +42,12 @@
 // in the lane-owned mapping, whose rows each cost broadcasts, weights and
 // totals beside their two multiply-adds per pixel; at 32x32 px ~400 and 88
 // against ~1050.  Measured on one MI355X against the lane-owned, narrow and
-// wide mappings these launches took before: 1M spots of 15x15 0.866 ms (1.038),
-// 500k of 32x32 1.41 (2.15), 2M of 7..32 px in one launch 3.47 (4.59), 10,000
-// of 21x21 0.070 (0.168), 10,007 of 7..32 px 0.107 (0.592), 1,024 of 11x11
-// 0.0195 (0.0505).
+// wide mappings these launches took before: 1M spots of 15x15 0.860 ms (1.037),
+// 500k of 32x32 1.41 (2.14), 2M of 7..32 px in one launch 3.20 (4.60), 200,000
+// floats of 17x17 0.584 (0.885), 10,000 of 21x21 0.069 (0.168), 10,007 of 7..32
+// px 0.082 (0.591), 1,024 of 11x11 0.0184 (0.0509).  Passes of mixed shapes in
+// straight-line code for their largest spot's tiles, ordered by size, against a
+// branch per tile in the order of the slots: 3.20 (3.47) and 0.082 (0.110).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -241,6 +245,12 @@ __device__ __forceinline__ void unrolled(F&& f) {
   }
 }
 
+// Tiles of a shape's larger side.
+__device__ __forceinline__ int tiles_of(uint32_t geo) {
+  const int w = geo & 0xff, h = (geo >> 8) & 0xff;
+  return ((w > h ? w : h) + 3) >> 2;
+}
+
 // Where a lane reads its pixels of a spot: CH windows of 4 columns.  A window
 // that reaches past its row's end goes on in the next row, still inside the
 // spot (its columns there have V = 0); on the last row it starts `over` pixels
@@ -269,14 +279,8 @@ struct Window {
   }
 };
 
-// The smallest and the largest of a per-block value (the same on the 16 lanes
-// of a block) over the wavefront's four blocks.
-__device__ __forceinline__ int min_over_blocks(int v) {
-  const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 4);
-  const int c = __builtin_amdgcn_readlane(v, 8), d = __builtin_amdgcn_readlane(v, 12);
-  const int e = a < b ? a : b, f = c < d ? c : d;
-  return e < f ? e : f;
-}
+// The largest of a per-block value (the same on the 16 lanes of a block) over
+// the wavefront's four blocks.
 __device__ __forceinline__ int max_over_blocks(int v) {
   const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 4);
   const int c = __builtin_amdgcn_readlane(v, 8), d = __builtin_amdgcn_readlane(v, 12);
@@ -423,10 +427,11 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
     for (int q = 0; q < CH; ++q) to[q].load(base[q] + (rb < win.last[q] ? rb : win.last[q]));
     rb += win.step;
   };
-  // the last row tile holds the last row: windows cut off there come back
+  // the last row tile holds the last row (of two: either): windows cut off there
+  // come back
   auto put_back = [&](auto ai, Raw<DT> (&row)[CH]) {
     constexpr int at = decltype(ai)::value;
-    if constexpr (at == TB - 1) {
+    if constexpr (at == TB - 1 || TB == 2) {
 #pragma unroll
       for (int q = 0; q < CH; ++q) row[q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
     }
@@ -442,7 +447,7 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   };
   auto add_row = [&](auto ai, const Raw<DT> (&row)[CH], double& sg, double& sgg) {
     constexpr int at = decltype(ai)::value;
-    const bool rowin = at < TB - 1 || 4 * at + ln.v < win.h;
+    const bool rowin = (at < TB - 1 && TB > 2) || 4 * at + ln.v < win.h;
     unrolled<TB>([&](auto bi) {
       constexpr int t = decltype(bi)::value;
       const double g = row[t / 4].template get<t % 4>();
@@ -505,7 +510,7 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
     });
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (!kRing) {
-      put_back(std::integral_constant<int, TB - 1>{}, px[TB - 1]);
+      unrolled<TB>([&](auto ai) { put_back(ai, px[decltype(ai)::value]); });
       if (p < cnt_new) {
         double sg = 0.0, sgg = 0.0;
         unrolled<TB>([&](auto ai) {
@@ -620,163 +625,82 @@ __device__ __forceinline__ void sum_residuals(const void* data, Shared<NS>& L, i
   }
 }
 
-// The same for slots of any shapes up to 16 CH pixels a side: each pass goes
-// over the tiles of its largest spot.  The tiles that a spot does not have add
-// zeros to its sums, so it has the same bits in every company.
-template <int NS, int CH, int DT>
-__device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, int cnt, int cnt_new) {
-  constexpr int NT = 4 * CH;  // tiles per side
-  int lane = __lane_id();
-  asm volatile("" : "+v"(lane));
-  const Lane ln(lane);
-#pragma unroll 1
-  for (int p = 0; p < cnt; p += 4) {
-    const int slot = L.order[p + ln.blk < cnt ? p + ln.blk : cnt - 1];
-    const double x = L.x[slot], y = L.y[slot], hx = L.hx[slot], hy = L.hy[slot];
-    const uint32_t geo = L.geo[slot];
-    Window<CH, DT> win;
-    win.set(geo, ln.v, ln.k);
-    const char* base = static_cast<const char*>(data) + L.off[slot] * Raw<DT>::kSize;
-    const int Tm = max_over_blocks((win.w + 3) >> 2), Hm = max_over_blocks((win.h + 3) >> 2);
-    const int Hs = min_over_blocks((win.h - 1) >> 2);  // the first tile with a last row
-    Raw<DT> px[NT][CH];
-    uint32_t rb = win.row;
-    unrolled<NT>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
-      if (at < Hm) {
-#pragma unroll
-        for (int q = 0; q < CH; ++q)
-          if (q == 0 || Tm > 4 * q)
-            px[at][q].load(base + win.start[q] * Raw<DT>::kSize + (rb < win.last[q] ? rb : win.last[q]));
-        rb += win.step;
-      }
-    });
-    double exq[CH], eyq[CH], V[NT], E[NT];
-    double R = 0.0, GX = 0.0, GY = 0.0;
-    unrolled<CH>([&](auto qi) {
-      constexpr int q = decltype(qi)::value;
-      exq[q] = eyq[q] = 0.0;
-      if (q == 0 || Tm > 4 * q || Hm > 4 * q) factors<q>(ln, win, x, y, hx, hy, exq[q], eyq[q]);
-    });
-    const double dy0 = double(ln.k) - y;
-    unrolled<NT>([&](auto ti) {
-      constexpr int t = decltype(ti)::value;
-      if (t < 1 || t < Tm) {
-        const double dx = (double(win.start[t / 4]) - x) + double(t % 4);
-        V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
-        GX = mfma4(V[t], V[t], GX);
-      }
-      if (t < 1 || t < Hm) {
-        E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
-        GY = mfma4(E[t], E[t], GY);
-      }
-    });
-    unrolled<NT>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
-      if (at >= Hs && at < Hm) {
-        asm volatile("");  // a branch, not a selected shift
-#pragma unroll
-        for (int q = 0; q < CH; ++q) px[at][q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
-      }
-    });
-    if (p < cnt_new) {
-      double sg = 0.0, sgg = 0.0;
-      unrolled<NT>([&](auto ai) {
-        constexpr int at = decltype(ai)::value;
-        if (at < Hm) {
-          const bool rowin = 4 * at + ln.v < win.h;
-          Raw<DT> row[CH];
-#pragma unroll
-          for (int q = 0; q < CH; ++q) row[q] = px[at][q].fresh();
-          unrolled<NT>([&](auto bi) {
-            constexpr int t = decltype(bi)::value;
-            if (t % 4 == 0 || t < Tm) {
-              const double g = row[t / 4].template get<t % 4>();
-              const double gm = rowin && t % 4 < win.own[t / 4] ? g : 0.0;
-              sg += gm;
-              sgg = __builtin_fma(gm, gm, sgg);
-            }
-          });
-        }
-      });
-      put_pixel_sums(ln, L, slot, p + ln.blk < cnt_new, sg, sgg);
-    }
-    unrolled<NT>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
-      if (at < 1 || at < Hm) {
-        double S = 0.0;
-        unrolled<NT>([&](auto bi) {
-          constexpr int t = decltype(bi)::value;
-          if (t < 1 || t < Tm) S = mfma4(px[at][t / 4].template get<t % 4>(), V[t], S);
-        });
-        R = mfma4(E[at], S, R);
-      }
-    });
-    put_totals(ln, L, slot, R, GX, GY);
-    if constexpr (DT != SPOTFIT_U16) {
-      wave_lds_sync();
-      const Amplitudes am = slot_amplitudes(L, slot, win.w, win.h);
-      double c2s = 0.0;
-      unrolled<CH>([&](auto qi) {
-        constexpr int q = decltype(qi)::value;
-        if (q == 0 || Tm > 4 * q) {
-          double aex[4], cs[4];
-          unrolled<4>([&](auto bi) {
-            constexpr int t = decltype(bi)::value;
-            aex[t] = am.a * lg::gbcast<4, t>(exq[q]);
-            cs[t] = 0.0;
-          });
-          unrolled<NT>([&](auto ai) {
-            constexpr int at = decltype(ai)::value;
-            if (at < Hm) residual_row<at, 4>(ln, px[at][q].fresh(), aex, eyq[at / 4], am.b, win.h, cs);
-          });
-          unrolled<4>([&](auto bi) {
-            constexpr int t = decltype(bi)::value;
-            c2s += t < win.own[q] ? cs[t] : 0.0;
-          });
-        }
-      });
-      c2s = block_sum(c2s);
-      if (ln.v == 0 && ln.k == 0) L.tot[kChi][slot] = c2s;
-    }
-  }
-}
-
-// A wavefront of 4 slots: block b evaluates slot b, whose candidate and pixels
-// (shifted into place) its lanes hold in registers from step to step, so a step
-// neither reads memory nor waits for it.  A lone wavefront per SIMD is bound by
-// that chain of latencies: 32 markers of 13x13 px 38.6 us a replayed frame (40.6
-// with the pixels read at each step), 1,024 of 11x11 18.0 (19.5), 640 raw spots
-// of 9..21 px 41.0 (47.3).
 struct Candidate {
   double x, y, hx, hy;
 };
 
-// One pass over the 4 slots at their candidates, into L.tot.  load: read the
-// pixels of every slot first, at `off`; some slot (fresh) is then a new spot.
-// Every slot has at most TB columns per lane group and TB row tiles; the tiles
-// that a smaller one does not have add zeros to its sums.
-template <int CH, int DT, int TB>
-__device__ __forceinline__ void evaluate_blocks(const void* data, Shared<4>& L, Raw<DT> (&px)[4 * CH][CH],
-                                                const Candidate& c, int64_t off, uint32_t geo, bool load,
-                                                bool fresh) {
+// One pass over four slots of any shapes (this lane's block has `slot`, of shape
+// geo) at their candidates, into L.tot.  load: read their pixels first, at `off`,
+// into px, shifted into place; else px holds them.  sums: some slot (fresh) is a
+// new spot.  Every slot has at most TB columns per lane group and TB row tiles;
+// the tiles that a smaller one does not have add zeros to its sums, so it has
+// the same bits in every company.
+//
+// A wavefront of 4 slots keeps px from step to step, so a step neither reads
+// memory nor waits for it.  A lone wavefront per SIMD is bound by that chain of
+// latencies: 32 markers of 13x13 px 38.6 us a replayed frame (40.6 with the
+// pixels read at each step), 1,024 of 11x11 18.0 (19.5), 4,000 raw spots of
+// 9..21 px 41.0 (47.3).  Of more slots, wide floats go through a ring of row tiles as
+// in evaluate_uniform.
+template <int NS, int CH, int DT, int TB>
+__device__ __forceinline__ void evaluate_pass(const void* data, Shared<NS>& L, int slot,
+                                              Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
+                                              uint32_t geo, bool load, bool sums, bool fresh) {
   constexpr int CQ = (TB + 3) / 4;
+  constexpr bool kFloat = DT != SPOTFIT_U16, kRing = NS > 4 && kFloat && CQ > 1;
+  constexpr int kRows = kRing ? 4 : TB;
   int lane = __lane_id();
   asm volatile("" : "+v"(lane));
   const Lane ln(lane);
   Window<CQ, DT> win;
   win.set(geo, ln.v, ln.k);
-  if (load) {
-    const char* base = static_cast<const char*>(data) + off * Raw<DT>::kSize;
-    uint32_t rb = win.row;
-    unrolled<TB>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
+  const char* base = static_cast<const char*>(data) + off * Raw<DT>::kSize;
+  uint32_t rb = win.row;
+  auto load_next = [&](Raw<DT> (&to)[CH]) {
 #pragma unroll
-      for (int q = 0; q < CQ; ++q)
-        px[at][q].load(base + win.start[q] * Raw<DT>::kSize + (rb < win.last[q] ? rb : win.last[q]));
-      rb += win.step;
+    for (int q = 0; q < CQ; ++q)
+      to[q].load(base + win.start[q] * Raw<DT>::kSize + (rb < win.last[q] ? rb : win.last[q]));
+    rb += win.step;
+  };
+  // windows cut off by a spot's end come back
+  auto put_back = [&](auto ai, Raw<DT> (&row)[CH]) {
+    constexpr int at = decltype(ai)::value;
+#pragma unroll
+    for (int q = 0; q < CQ; ++q) row[q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
+  };
+  auto refill = [&](auto ii) {  // after item i of the ring
+    constexpr int i = decltype(ii)::value + kRows;
+    if constexpr (i < 2 * TB) {
+      if constexpr (i == TB) rb = win.row;
+      load_next(px[i % kRows]);
+    }
+  };
+  auto add_row = [&](auto ai, const Raw<DT> (&row)[CH], double& sg, double& sgg) {
+    constexpr int at = decltype(ai)::value;
+    const bool rowin = 4 * at + ln.v < win.h;
+    unrolled<TB>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      const double g = row[t / 4].template get<t % 4>();
+      const double gm = rowin && t % 4 < win.own[t / 4] ? g : 0.0;
+      sg += gm;
+      sgg = __builtin_fma(gm, gm, sgg);
     });
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  if constexpr (kRing) {
+    if (sums) {
+      double sg = 0.0, sgg = 0.0;
+      unrolled<TB>([&](auto ai) {
+        Raw<DT> row[CH];
+        load_next(row);
+        put_back(ai, row);
+        add_row(ai, row, sg, sgg);
+      });
+      put_pixel_sums(ln, L, slot, fresh, sg, sgg);
+      rb = win.row;
+    }
   }
+  if (load) unrolled<kRows>([&](auto ai) { load_next(px[decltype(ai)::value]); });
   double exq[CQ], eyq[CQ], V[TB], E[TB];
   double R = 0.0, GX = 0.0, GY = 0.0;
   unrolled<CQ>([&](auto qi) {
@@ -792,68 +716,109 @@ __device__ __forceinline__ void evaluate_blocks(const void* data, Shared<4>& L, 
     E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
     GY = mfma4(E[t], E[t], GY);
   });
-  if (load) {  // the windows cut off by a spot's end
-    unrolled<TB>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
+  if constexpr (!kRing) {
+    if (load) unrolled<TB>([&](auto ai) { put_back(ai, px[decltype(ai)::value]); });
+    if (sums) {
+      double sg = 0.0, sgg = 0.0;
+      unrolled<TB>([&](auto ai) {
+        constexpr int at = decltype(ai)::value;
+        Raw<DT> row[CH];
 #pragma unroll
-      for (int q = 0; q < CQ; ++q) px[at][q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
-    });
-    double sg = 0.0, sgg = 0.0;
-    unrolled<TB>([&](auto ai) {
-      constexpr int at = decltype(ai)::value;
-      const bool rowin = 4 * at + ln.v < win.h;
-      Raw<DT> row[CQ];
-#pragma unroll
-      for (int q = 0; q < CQ; ++q) row[q] = px[at][q].fresh();
-      unrolled<TB>([&](auto bi) {
-        constexpr int t = decltype(bi)::value;
-        const double g = row[t / 4].template get<t % 4>();
-        const double gm = rowin && t % 4 < win.own[t / 4] ? g : 0.0;
-        sg += gm;
-        sgg = __builtin_fma(gm, gm, sgg);
+        for (int q = 0; q < CQ; ++q) row[q] = px[at][q].fresh();
+        add_row(ai, row, sg, sgg);
       });
-      __builtin_amdgcn_sched_barrier(0);
-    });
-    put_pixel_sums(ln, L, ln.blk, fresh, sg, sgg);
+      put_pixel_sums(ln, L, slot, fresh, sg, sgg);
+    }
   }
   unrolled<TB>([&](auto ai) {
     constexpr int at = decltype(ai)::value;
+    if constexpr (kRing) put_back(ai, px[at % kRows]);
     Raw<DT> row[CQ];
 #pragma unroll
-    for (int q = 0; q < CQ; ++q) row[q] = px[at][q].fresh();
+    for (int q = 0; q < CQ; ++q) row[q] = px[at % kRows][q].fresh();
     double S = 0.0;
     unrolled<TB>([&](auto bi) {
       constexpr int t = decltype(bi)::value;
       S = mfma4(row[t / 4].template get<t % 4>(), V[t], S);
     });
     R = mfma4(E[at], S, R);
-    if constexpr (at % 2 == 1) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kRing) refill(ai);
+    if constexpr (kRing || at % 2 == 1) __builtin_amdgcn_sched_barrier(0);
   });
-  put_totals(ln, L, ln.blk, R, GX, GY);
-  if constexpr (DT != SPOTFIT_U16) {
+  put_totals(ln, L, slot, R, GX, GY);
+  if constexpr (kFloat) {
     wave_lds_sync();
-    const Amplitudes am = slot_amplitudes(L, ln.blk, win.w, win.h);
-    double c2s = 0.0;
-    unrolled<CQ>([&](auto qi) {
+    const Amplitudes am = slot_amplitudes(L, slot, win.w, win.h);
+    double aex[CQ][4], cs[CQ][4], c2s = 0.0;
+    auto scale = [&](auto qi) {
       constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
-      double aex[4], cs[4];
       unrolled<B>([&](auto bi) {
         constexpr int t = decltype(bi)::value;
-        aex[t] = am.a * lg::gbcast<4, t>(exq[q]);
-        cs[t] = 0.0;
+        aex[q][t] = am.a * lg::gbcast<4, t>(exq[q]);
+        cs[q][t] = 0.0;
       });
+    };
+    auto window = [&](auto ai, auto qi, const Raw<DT>& g) {
+      constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
+      residual_row<decltype(ai)::value, B>(ln, g.fresh(), aex[q], eyq[decltype(ai)::value / 4], am.b, win.h, cs[q]);
+    };
+    auto add_up = [&](auto qi) {
+      constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
+      unrolled<B>([&](auto bi) {
+        constexpr int t = decltype(bi)::value;
+        c2s += t < win.own[q] ? cs[q][t] : 0.0;
+      });
+    };
+    if constexpr (kRing) {  // row by row, as the ring goes
+      unrolled<CQ>(scale);
       unrolled<TB>([&](auto ai) {
-        constexpr int at = decltype(ai)::value;
-        residual_row<at, B>(ln, px[at][q].fresh(), aex, eyq[at / 4], am.b, win.h, cs);
+        constexpr int i = TB + decltype(ai)::value;
+        put_back(ai, px[i % kRows]);
+        unrolled<CQ>([&](auto qi) { window(ai, qi, px[i % kRows][decltype(qi)::value]); });
+        refill(std::integral_constant<int, i>{});
         __builtin_amdgcn_sched_barrier(0);
       });
-      unrolled<B>([&](auto bi) {
-        constexpr int t = decltype(bi)::value;
-        c2s += t < win.own[q] ? cs[t] : 0.0;
+      unrolled<CQ>(add_up);
+    } else {  // window by window: fewer registers
+      unrolled<CQ>([&](auto qi) {
+        scale(qi);
+        unrolled<TB>([&](auto ai) {
+          window(ai, qi, px[decltype(ai)::value][decltype(qi)::value]);
+          __builtin_amdgcn_sched_barrier(0);
+        });
+        add_up(qi);
       });
-    });
+    }
     c2s = block_sum(c2s);
-    if (ln.v == 0 && ln.k == 0) L.tot[kChi][ln.blk] = c2s;
+    if (ln.v == 0 && ln.k == 0) L.tot[kChi][slot] = c2s;
+  }
+}
+
+// The pass with the tiles of the largest of its four slots.
+template <int NS, int CH, int DT>
+__device__ __forceinline__ void evaluate_four(const void* data, Shared<NS>& L, int slot,
+                                              Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
+                                              uint32_t geo, bool load, bool sums, bool fresh) {
+  const int tiles = max_over_blocks(tiles_of(geo));
+  unrolled<4 * CH - 1>([&](auto ti) {
+    constexpr int TB = decltype(ti)::value + 2;
+    if (tiles == TB || (TB == 2 && tiles < 2))
+      evaluate_pass<NS, CH, DT, TB>(data, L, slot, px, c, off, geo, load, sums, fresh);
+  });
+}
+
+// Evaluates the cnt > 0 slots of L.order, of any shapes, four a pass.
+template <int NS, int CH, int DT>
+__device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, int cnt) {
+  const int blk = (__lane_id() >> 2) & 3;
+#pragma unroll 1
+  for (int p = 0; p < cnt; p += 4) {
+    const int slot = L.order[p + blk < cnt ? p + blk : cnt - 1];
+    const uint32_t geo = L.geo[slot];
+    const bool fresh = (geo & kGeoNew) != 0;
+    Raw<DT> px[4 * CH][CH];
+    evaluate_four<NS, CH, DT>(data, L, slot, px, Candidate{L.x[slot], L.y[slot], L.hx[slot], L.hy[slot]},
+                              L.off[slot], geo, true, __builtin_amdgcn_ballot_w64(fresh) != 0, fresh);
   }
 }
 
@@ -1096,46 +1061,50 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
     const uint64_t m_act = __builtin_amdgcn_ballot_w64(act && lead);
     const uint64_t m_new = __builtin_amdgcn_ballot_w64(fresh && lead);
     const int cnt = __builtin_popcountll(m_act);
-    if constexpr (!kBlocks) {
-      if (act) {
-        const int rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
-        L.order[rank] = own;
-      }
-      wave_lds_sync();
-      geo = L.geo[owner ? own : 0];
-    }
-    const int w = geo & 0xff, h = (geo >> 8) & 0xff;
+    int w = geo & 0xff, h = (geo >> 8) & 0xff;
     if (cnt > 0) {
-      const int cnt_new = __builtin_popcountll(m_new);
       const int lead0 = __builtin_ctzll(m_act);
-      const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0) & 0xffffu;
-      const int T = ((geo0 & 0xff) + 3) >> 2;
       if constexpr (kBlocks) {
-        // a block without a spot goes along on the first one's pixels
+        // block b evaluates slot b, from registers; a block without a spot goes
+        // along on the first one's pixels
         const int2 o = __builtin_bit_cast(int2, off);
         const int2 o0 = make_int2(__builtin_amdgcn_readlane(o.x, lead0), __builtin_amdgcn_readlane(o.y, lead0));
-        const int64_t at = act ? off : __builtin_bit_cast(int64_t, o0);
-        const uint32_t shape = act ? geo : geo0;
-        // tiles for the largest side of the four (at least 2)
-        const int side = (shape & 0xff) > (shape >> 8 & 0xff) ? shape & 0xff : shape >> 8 & 0xff;
-        const int tiles = max_over_blocks((side + 3) >> 2);
-        unrolled<4 * CH - 1>([&](auto ti) {
-          constexpr int TB = decltype(ti)::value + 2;
-          if (tiles == TB || (TB == 2 && tiles < 2))
-            evaluate_blocks<CH, DT, TB>(data, L, px, cand, at, shape, cnt_new != 0, fresh);
-        });
+        const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0);
+        evaluate_four<NS, CH, DT>(data, L, own, px, cand, act ? off : __builtin_bit_cast(int64_t, o0),
+                                  act ? geo : geo0, m_new != 0, m_new != 0, fresh);
       } else {
+        wave_lds_sync();
+        geo = L.geo[owner ? own : 0];
+        w = geo & 0xff;
+        h = (geo >> 8) & 0xff;
+        const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0) & 0xffffu;
+        const int T = ((geo0 & 0xff) + 3) >> 2;
         const bool uni = T == (int)((geo0 >> 8) + 3) >> 2 &&
                          __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
-        bool done = false;
-        unrolled<4 * CH - 1>([&](auto ti) {
-          constexpr int TB = decltype(ti)::value + 2;
-          if (uni && T == TB) {
-            evaluate_uniform<NS, DT, TB>(data, L, cnt, cnt_new, geo0);
-            done = true;
+        int rank = 0;
+        if (uni) {  // new spots first, so that few passes form their sums of g and g^2
+          rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
+        } else {  // by size, so that few passes go over the tiles of a large spot
+          const int tiles = tiles_of(geo);
+          int before = 0;
+#pragma unroll
+          for (int t = 4 * CH; t >= 1; --t) {
+            const uint64_t m = __builtin_amdgcn_ballot_w64(act && tiles == t);
+            if (tiles == t) rank = before + rank_of(m);
+            before += __builtin_popcountll(m);
           }
-        });
-        if (!done) evaluate_any<NS, CH, DT>(data, L, cnt, cnt_new);
+        }
+        if (act) L.order[rank] = own;
+        wave_lds_sync();
+        if (uni) {
+          const int cnt_new = __builtin_popcountll(m_new);
+          unrolled<4 * CH - 1>([&](auto ti) {
+            constexpr int TB = decltype(ti)::value + 2;
+            if (T == TB || (TB == 2 && T < 2)) evaluate_uniform<NS, DT, TB>(data, L, cnt, cnt_new, geo0);
+          });
+        } else {
+          evaluate_any<NS, CH, DT>(data, L, cnt);
+        }
       }
       wave_lds_sync();
     }
@@ -1410,7 +1379,7 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
 }
 
 template <int NS, int CH, int DT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(NS == 16 && CH == 1 ? 3 : 2))) void fit_matrix_kernel(
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 && (NS == 4 || (NS == 16 && DT == SPOTFIT_U16)) ? 3 : 2))) void fit_matrix_kernel(
     KArgs /* read through args() */, MatrixQueue mq) {
   __shared__ Shared<NS> lds;
   fit_matrix<NS, CH, DT>(mq, lds);
@@ -1421,8 +1390,9 @@ __global__ void matrix_queue_reset_kernel(int32_t* take) {
 }
 
 template <int NS, int CH>
-static const void* symbol() {
-  return reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_U16>);
+static const void* symbol(int dtype) {
+  return dtype == SPOTFIT_U16 ? reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_U16>)
+                              : reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_F32>);
 }
 
 template <int NS, int CH>
@@ -1436,11 +1406,12 @@ static hipError_t launch(const KArgs& ka, const MatrixQueue& mq, int grid, hipSt
 
 }  // namespace mtx
 
-#define SF_MATRIX_SHAPES(X) X(4, 1) X(16, 1) X(64, 1) X(4, 2) X(16, 2) X(64, 2)
+#define SF_MATRIX_SHAPES(X) \
+  X(4, 1) X(16, 1) X(32, 1) X(64, 1) X(4, 2) X(16, 2) X(32, 2) X(64, 2)
 
-const void* matrix_kernel_symbol(int slots, bool wide) {
+const void* matrix_kernel_symbol(int slots, bool wide, int dtype) {
 #define SF_MXSYM(NS, CH) \
-  if (slots == NS && wide == (CH == 2)) return mtx::symbol<NS, CH>();
+  if (slots == NS && wide == (CH == 2)) return mtx::symbol<NS, CH>(dtype);
   SF_MATRIX_SHAPES(SF_MXSYM)
 #undef SF_MXSYM
   return nullptr;

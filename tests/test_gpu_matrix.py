@@ -114,3 +114,16 @@ def test_retries_evaluate_the_best_point_again():
     r = oracle.fit_batch(b, oracle.default_opts(), threads=8)
     k = compare(a, r, chi_band=1e-11, step_band=1e-9)
     assert k["strict_mismatch"] == 0
+
+
+@pytest.mark.parametrize("n", [12289, 40001, 262200])
+def test_batch_sizes_of_every_build(n):
+    """Batches that take 16, 32 and 64 spots per wavefront by themselves, the last
+    of them through the sorted class lists: the bits of the same spots in a small
+    batch.  Every spot is in the batch several times, on one copy of its pixels."""
+    _, b, _ = _shapes([(3, 4), (4, 4), (7, 7), (8, 9), (9, 9), (12, 17), (25, 17)], 121)
+    m = b.sizes.shape[0]
+    t = np.arange(n) % m
+    big = spotgen.SpotBatch(b.data, b.sizes[t], b.offsets[t], b.init[t], b.truth, "tiled")
+    ref = _fit(b, 4, schedule=1)
+    _equal(_fit(big, schedule=1), {k: v[t] for k, v in ref.items()})
