@@ -35,7 +35,7 @@ struct spotfit_ctx {
   int matrix_slots;      // SPOTFIT_MATRIX_SLOTS override: one of kMatrixSlots; else 0
   int32_t* ws;      // counters[8] then 3 lists of ws_cap spot indices
   int64_t ws_cap;
-  unsigned long long* stats;  // device histogram buffer of spotfit_get_stats
+  void* stats;  // host memory that the blocks of spotfit_get_stats write
   int32_t* queue;             // spot counter of the narrow kernel's uniform launches
   int32_t* scratch;           // device address of this device's copy of `scratch` (below)
 };
@@ -105,40 +105,66 @@ int ppl_index(int ppl) {
   }
 }
 
-// spotfit_get_stats device buffer: n, status[6], iterations[65], grad, trial
-constexpr int kStatsLen = 1 + 6 + 65 + 2;
+// One block's share of spotfit_get_stats.
+struct StatsBlock {
+  uint32_t status[6], iters[65], pad;
+  unsigned long long evals[2];
+};
+constexpr int kStatsBlocks = 128, kStatsThreads = 1024;
+constexpr int64_t kStatsSpots = 4096;  // spots per block, up to kStatsBlocks
 
-__global__ void stats_zero_kernel(unsigned long long* buf) {
-  if (threadIdx.x < kStatsLen) buf[threadIdx.x] = 0ull;
-}
-
-__global__ __launch_bounds__(256) void stats_kernel(const int32_t* status, const int32_t* iters,
-                                                     const int32_t* evals, int64_t n,
-                                                     unsigned long long* buf) {
-  __shared__ unsigned int hist[6 + 65];
+// Every block leaves its counts in host memory and the host adds them up once the
+// stream is done: no buffer to clear, no copy, and no atomics on the same 74
+// words from every block, which pass one by one (about 50 ns each: of 100,000 spots
+// the counting took 12.3 us and the clearing 4.7, and start values, fit and
+// statistics together went from 161.7 us to 145.2).  The counts of a block are in
+// kCopies histograms by lane, so that the lanes of a wavefront, mostly with the
+// same few values, collide less.
+__global__ __launch_bounds__(kStatsThreads) void stats_kernel(const int32_t* status, const int32_t* iters,
+                                                              const int32_t* evals, int64_t n,
+                                                              StatsBlock* out) {
+  constexpr int kCopies = 16, kBins = 6 + 65, kPitch = kBins + 2;
+  __shared__ uint32_t hist[kCopies * kPitch];
   __shared__ unsigned long long ev[2];
-  for (int i = threadIdx.x; i < 6 + 65; i += blockDim.x) hist[i] = 0u;
+  for (int i = threadIdx.x; i < kCopies * kPitch; i += kStatsThreads) hist[i] = 0u;
   if (threadIdx.x < 2) ev[threadIdx.x] = 0ull;
   __syncthreads();
+  uint32_t* mine = hist + (threadIdx.x % kCopies) * kPitch;
   unsigned long long gsum = 0, tsum = 0;
-  for (int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; s < n;
-       s += (int64_t)gridDim.x * blockDim.x) {
-    const int st = status[s];
-    if (st >= 0 && st < 6) atomicAdd(&hist[st], 1u);
-    const int it = iters[s];
-    atomicAdd(&hist[6 + (it < 0 ? 0 : it > 64 ? 64 : it)], 1u);
+  for (int64_t s = (int64_t)blockIdx.x * kStatsThreads + threadIdx.x; s < n;
+       s += (int64_t)gridDim.x * kStatsThreads) {
+    const int st = status[s], it = iters[s];
+    int32_t ng = 0, nt = 0;
     if (evals) {
-      gsum += (unsigned long long)(evals[2 * s] > 0 ? evals[2 * s] : 0);
-      tsum += (unsigned long long)(evals[2 * s + 1] > 0 ? evals[2 * s + 1] : 0);
+      ng = evals[2 * s];
+      nt = evals[2 * s + 1];
+    }
+    if (st >= 0 && st < 6) atomicAdd(&mine[st], 1u);
+    atomicAdd(&mine[6 + (it < 0 ? 0 : it > 64 ? 64 : it)], 1u);
+    gsum += (unsigned long long)(ng > 0 ? ng : 0);
+    tsum += (unsigned long long)(nt > 0 ? nt : 0);
+  }
+  if (evals) {
+    for (int d = 32; d > 0; d >>= 1) {
+      gsum += __shfl_down(gsum, d);
+      tsum += __shfl_down(tsum, d);
+    }
+    if (threadIdx.x % 64 == 0) {
+      atomicAdd(&ev[0], gsum);
+      atomicAdd(&ev[1], tsum);
     }
   }
-  if (gsum) atomicAdd(&ev[0], gsum);
-  if (tsum) atomicAdd(&ev[1], tsum);
   __syncthreads();
-  for (int i = threadIdx.x; i < 6 + 65; i += blockDim.x)
-    if (hist[i]) atomicAdd(&buf[1 + i], (unsigned long long)hist[i]);
-  if (threadIdx.x < 2 && ev[threadIdx.x]) atomicAdd(&buf[1 + 6 + 65 + threadIdx.x], ev[threadIdx.x]);
-  if (blockIdx.x == 0 && threadIdx.x == 0) buf[0] = (unsigned long long)n;
+  StatsBlock& b = out[blockIdx.x];
+  if (threadIdx.x < kBins) {
+    uint32_t v = 0;
+    for (int c = 0; c < kCopies; ++c) v += hist[c * kPitch + threadIdx.x];
+    if (threadIdx.x < 6)
+      b.status[threadIdx.x] = v;
+    else
+      b.iters[threadIdx.x - 6] = v;
+  }
+  if (threadIdx.x < 2) b.evals[threadIdx.x] = ev[threadIdx.x];
 }
 
 // y = e^x with the fit kernels' own exponential (grid-stride over n values)
@@ -289,10 +315,10 @@ int spotfit_ctx_create(spotfit_ctx_t** out, int device) {
     delete c;
     return fail_hip(e, "hipGetSymbolAddress (no-allocation scratch)");
   }
-  e = hipMalloc((void**)&c->stats, sizeof(unsigned long long) * kStatsLen);
+  e = hipHostMalloc(&c->stats, sizeof(StatsBlock) * kStatsBlocks, hipHostMallocMapped);
   if (e == hipSuccess) e = hipMalloc((void**)&c->queue, sizeof(int32_t) * sf::kMatrixCounters * sf::kMatrixCounterWords);
   if (e != hipSuccess) {
-    if (c->stats) (void)hipFree(c->stats);
+    if (c->stats) (void)hipHostFree(c->stats);
     delete c;
     return fail_hip(e, "hipMalloc (context buffers)");
   }
@@ -332,7 +358,7 @@ void spotfit_ctx_destroy(spotfit_ctx_t* ctx) {
     (void)hipGetDevice(&cur);
     (void)hipSetDevice(ctx->device);
     if (ctx->ws) (void)hipFree(ctx->ws);
-    if (ctx->stats) (void)hipFree(ctx->stats);
+    if (ctx->stats) (void)hipHostFree(ctx->stats);
     if (ctx->queue) (void)hipFree(ctx->queue);
     if (cur >= 0) (void)hipSetDevice(cur);
   }
@@ -782,23 +808,25 @@ int spotfit_get_stats(spotfit_ctx_t* ctx, const int32_t* status, const int32_t* 
   if (n == 0) return SPOTFIT_OK;
   if (!status || !iters) return fail(SPOTFIT_E_NULL, "get_stats: NULL array");
   hipStream_t st = (hipStream_t)stream;
-  hipLaunchKernelGGL(stats_zero_kernel, dim3(1), dim3(128), 0, st, ctx->stats);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return fail_hip(e, "statistics kernel launch");
-  const int64_t blocks = (n + 255) / 256;
-  hipLaunchKernelGGL(stats_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256), 0, st,
-                     status, iters, evals, n, ctx->stats);
+  const int64_t want = (n + kStatsSpots - 1) / kStatsSpots;
+  const int blocks = (int)(want < kStatsBlocks ? want : kStatsBlocks);
+  void* dev = nullptr;
+  hipError_t e = hipHostGetDevicePointer(&dev, ctx->stats, 0);
+  if (e != hipSuccess) return fail_hip(e, "statistics buffer");
+  hipLaunchKernelGGL(stats_kernel, dim3((unsigned)blocks), dim3(kStatsThreads), 0, st, status, iters,
+                     evals, n, static_cast<StatsBlock*>(dev));
   e = hipGetLastError();
   if (e != hipSuccess) return fail_hip(e, "statistics kernel launch");
-  unsigned long long h[kStatsLen];
-  e = hipMemcpyAsync(h, ctx->stats, sizeof h, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess) e = hipStreamSynchronize(st);
-  if (e != hipSuccess) return fail_hip(e, "statistics copy");
-  out->n_spots = (int64_t)h[0];
-  for (int i = 0; i < 6; ++i) out->status_count[i] = (int64_t)h[1 + i];
-  for (int i = 0; i < 65; ++i) out->iters_hist[i] = (int64_t)h[7 + i];
-  out->grad_evals = (int64_t)h[72];
-  out->trial_evals = (int64_t)h[73];
+  e = hipStreamSynchronize(st);
+  if (e != hipSuccess) return fail_hip(e, "statistics kernel");
+  const StatsBlock* h = static_cast<const StatsBlock*>(ctx->stats);
+  out->n_spots = n;
+  for (int k = 0; k < blocks; ++k) {
+    for (int i = 0; i < 6; ++i) out->status_count[i] += h[k].status[i];
+    for (int i = 0; i < 65; ++i) out->iters_hist[i] += h[k].iters[i];
+    out->grad_evals += (int64_t)h[k].evals[0];
+    out->trial_evals += (int64_t)h[k].evals[1];
+  }
   return SPOTFIT_OK;
 }
 
