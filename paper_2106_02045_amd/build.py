@@ -16,7 +16,7 @@ CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 SOURCES = ["spotfit_kernels.hip", "spotfit_group.hip", "spotfit_narrow.hip", "spotfit_init.hip",
            "spotfit_plain.hip", "spotfit_owned.hip", "spotfit_matrix.hip", "spotfit_api.hip",
-           "spotfit_serve.hip", "spotfit_track.hip"]
+           "spotfit_serve.hip", "spotfit_track.hip", "spotfit_copy.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 OUT = os.path.join(HERE, "libspotfit.so")
 

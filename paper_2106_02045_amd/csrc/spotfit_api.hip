@@ -1004,13 +1004,39 @@ int spotfit_graph_create(spotfit_graph_t** out, spotfit_ctx_t* ctx, const void* 
     spotfit_graph_destroy(g);
     return fail_hip(e, "hipStreamCreateWithFlags");
   }
+  // the host's arrays as `io` names them: the copies of small ones are one kernel
+  // before the fit and one after it
+  struct Copy {
+    void* dst;
+    const void* src;
+    int64_t bytes;
+  };
+  const Copy in[2] = {{const_cast<void*>(data), io ? io->data : nullptr, io ? io->data_bytes : 0},
+                      {const_cast<float*>(init), io ? io->init : nullptr, 16 * n}};
+  const Copy back[4] = {{io ? io->params : nullptr, params_out, 24 * n},
+                        {io ? io->chi2 : nullptr, chi2_out, 4 * n},
+                        {io ? io->iters : nullptr, iters_out, 4 * n},
+                        {io ? io->status : nullptr, status_out, 4 * n}};
+  sf::CopyList in_list{}, back_list{};
+  bool in_kernel = true, back_kernel = true;
+  for (const Copy& c : in) {
+    if (!c.src) continue;
+    const void* p = sf::pinned_address(c.src, c.bytes);
+    in_kernel = in_kernel && p && in_list.add(c.dst, p, c.bytes);
+  }
+  for (const Copy& c : back) {
+    if (!c.dst) continue;
+    void* p = sf::pinned_address(c.dst, c.bytes);
+    back_kernel = back_kernel && p && back_list.add(p, c.src, c.bytes);
+  }
   e = hipStreamBeginCapture(st, hipStreamCaptureModeThreadLocal);
-  if (e == hipSuccess && io && io->data)
-    e = hipMemcpyAsync(const_cast<void*>(data), io->data, (size_t)io->data_bytes,
-                       hipMemcpyHostToDevice, st);
-  if (e == hipSuccess && io && io->init)
-    e = hipMemcpyAsync(const_cast<float*>(init), io->init, sizeof(float) * 4 * (size_t)n,
-                       hipMemcpyHostToDevice, st);
+  if (e == hipSuccess && in_kernel) {
+    e = sf::launch_copy(in_list, st);
+  } else {
+    for (const Copy& c : in)
+      if (e == hipSuccess && c.src)
+        e = hipMemcpyAsync(c.dst, c.src, (size_t)c.bytes, hipMemcpyHostToDevice, st);
+  }
   rc = SPOTFIT_OK;
   if (e == hipSuccess && raw)
     rc = launch_raw(ctx, data, dtype, sizes, offsets, n, o, g->init_buf, params_out, chi2_out,
@@ -1018,14 +1044,13 @@ int spotfit_graph_create(spotfit_graph_t** out, spotfit_ctx_t* ctx, const void* 
   else if (e == hipSuccess)
     rc = launch_fit(ctx, data, dtype, sizes, offsets, init, n, o, params_out, chi2_out, iters_out,
                     status_out, nullptr, st, nullptr, nullptr, mixed ? &gws : nullptr);
-  if (e == hipSuccess && rc == SPOTFIT_OK && io && io->params)
-    e = hipMemcpyAsync(io->params, params_out, sizeof(float) * 6 * (size_t)n, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess && rc == SPOTFIT_OK && io && io->chi2)
-    e = hipMemcpyAsync(io->chi2, chi2_out, sizeof(float) * (size_t)n, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess && rc == SPOTFIT_OK && io && io->iters)
-    e = hipMemcpyAsync(io->iters, iters_out, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st);
-  if (e == hipSuccess && rc == SPOTFIT_OK && io && io->status)
-    e = hipMemcpyAsync(io->status, status_out, sizeof(int32_t) * (size_t)n, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess && rc == SPOTFIT_OK && back_kernel) {
+    e = sf::launch_copy(back_list, st);
+  } else {
+    for (const Copy& c : back)
+      if (e == hipSuccess && rc == SPOTFIT_OK && c.dst)
+        e = hipMemcpyAsync(c.dst, c.src, (size_t)c.bytes, hipMemcpyDeviceToHost, st);
+  }
   // always end the capture, so the stream leaves capture mode whatever failed
   const hipError_t e_end = hipStreamEndCapture(st, &g->graph);
   if (e == hipSuccess) e = e_end;

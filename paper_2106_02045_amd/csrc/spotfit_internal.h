@@ -157,4 +157,20 @@ hipError_t launch_start_values(int method, const void* data, int dtype, const sp
                                const int64_t* offsets, int64_t n, int max_side, int max_pixels,
                                float* out, hipStream_t st);
 
+// Up to kCopyMax arrays to copy with one kernel launch, kCopyBytes at most in
+// all (there the engine's hand-over still costs a fifth more): `add` takes one if
+// it still fits.  Host arrays by the device's address.
+constexpr int kCopyMax = 4;
+constexpr int64_t kCopyBytes = 1 << 20;
+struct CopyList {
+  const void* src[kCopyMax];
+  void* dst[kCopyMax];
+  int64_t bytes[kCopyMax];
+  int64_t total;
+  int count;
+  bool add(void* d, const void* s, int64_t n);
+};
+hipError_t launch_copy(const CopyList& list, hipStream_t st);
+void* pinned_address(const void* host, int64_t n);
+
 }  // namespace sf

@@ -107,6 +107,8 @@ struct spotfit_serve {
   float* h_init = nullptr;
   unsigned char *d_meta = nullptr, *h_meta = nullptr;
   unsigned char *d_res = nullptr, *h_res = nullptr;
+  // the device's addresses of h_pix, h_meta and h_res, for copies by a kernel
+  unsigned char *m_pix = nullptr, *m_meta = nullptr, *m_res = nullptr;
   int64_t pix_head = 0, pix_used = 0, spot_head = 0, spot_used = 0;
 
   // frame slots, FIFO by ticket
@@ -285,7 +287,9 @@ bool spotfit_serve::launch_ready() {
   hipStream_t st = streams[si];
   const bool injected = fail_batch > 0 && ++batches_started == fail_batch;
   // pixel bytes of the batch: frames are consecutive in the pixel ring except
-  // where it wrapped, so copy maximal contiguous runs
+  // where it wrapped, so copy maximal contiguous runs; a small batch's with one
+  // kernel, with the records below
+  sf::CopyList list{};
   hipError_t e = injected ? hipErrorUnknown : hipSuccess;
   if (!injected) {
     int64_t run0 = -1, run1 = -1;
@@ -298,7 +302,7 @@ bool spotfit_serve::launch_ready() {
           continue;
         }
       }
-      if (run0 >= 0)
+      if (run0 >= 0 && !list.add(d_pix + run0, m_pix + run0, run1 - run0))
         e = hipMemcpyAsync(d_pix + run0, h_pix + run0, (size_t)(run1 - run0), hipMemcpyHostToDevice, st);
       if (!last) {
         const FrameRec& f = rec(t);
@@ -316,6 +320,7 @@ bool spotfit_serve::launch_ready() {
     // the dispatcher thread otherwise spends while the GPU waits
     const FrameMeta m = frame_meta(d_pix + rec(t0).meta_off, nsp);
     const sf::MixedWs ws{m.counters, m.lists, nsp};
+    if (e == hipSuccess) e = sf::launch_copy(list, st);
     if (e == hipSuccess)
       rc = sf::fit_preclassified(ctxs[si], d_pix, dtype, m.sizes, m.offs, dev_init ? nullptr : m.init,
                                  dev_init ? m.init : nullptr, nsp, opt, ws, dv.params, dv.chi2,
@@ -326,9 +331,10 @@ bool spotfit_serve::launch_ready() {
     std::memcpy(hv.offs, h_offs + spot0, sizeof(int64_t) * nsp);
     std::memcpy(hv.sizes, h_sizes + spot0, sizeof(spotfit_shape_t) * nsp);
     if (!dev_init) std::memcpy(hv.init, h_init + 4 * spot0, sizeof(float) * 4 * nsp);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(dv.offs, hv.offs, (size_t)(dev_init ? 12 : kMetaBytes) * nsp,
-                         hipMemcpyHostToDevice, st);
+    const int64_t bytes = (dev_init ? 12 : kMetaBytes) * nsp;
+    if (e == hipSuccess && !list.add(d_meta + kMetaBytes * spot0, m_meta + kMetaBytes * spot0, bytes))
+      e = hipMemcpyAsync(dv.offs, hv.offs, (size_t)bytes, hipMemcpyHostToDevice, st);
+    if (e == hipSuccess) e = sf::launch_copy(list, st);
     if (e == hipSuccess && dev_init)  // start values on the device, in the fit's own launch
       rc = spotfit_fit_raw(ctxs[si], d_pix, dtype, dv.sizes, dv.offs, nsp, &opt, dv.init,
                            dv.params, dv.chi2, dv.iters, dv.status, nullptr, st);
@@ -356,8 +362,12 @@ bool spotfit_serve::launch_ready() {
                            hipMemcpyDeviceToHost, st);
     }
   }
-  if (e == hipSuccess && rc == SPOTFIT_OK)
-    e = hipMemcpyAsync(hv.params, dv.params, (size_t)kResBytes * nsp, hipMemcpyDeviceToHost, st);
+  if (e == hipSuccess && rc == SPOTFIT_OK) {
+    sf::CopyList back{};
+    e = back.add(m_res + kResBytes * spot0, dv.params, kResBytes * nsp)
+            ? sf::launch_copy(back, st)
+            : hipMemcpyAsync(hv.params, dv.params, (size_t)kResBytes * nsp, hipMemcpyDeviceToHost, st);
+  }
   Batch b;
   b.stream = si;
   b.first_ticket = t0;
@@ -571,6 +581,10 @@ int spotfit_serve_create(spotfit_serve_t** out, int device, const spotfit_option
     return cleanup(e, "record ring");
   if ((e = alloc_pair(&sv->d_res, &sv->h_res, spotfit_serve::kResBytes * sv->spot_cap)) != hipSuccess)
     return cleanup(e, "result ring");
+  for (auto p : {std::make_pair(&sv->m_pix, sv->h_pix), std::make_pair(&sv->m_meta, sv->h_meta),
+                 std::make_pair(&sv->m_res, sv->h_res)})
+    if ((e = hipHostGetDevicePointer((void**)p.first, p.second, 0)) != hipSuccess)
+      return cleanup(e, "ring addresses");
   for (int i = 0; i < n_streams; ++i) {
     hipStream_t st = nullptr;
     if ((e = hipStreamCreateWithFlags(&st, hipStreamNonBlocking)) != hipSuccess) return cleanup(e, "stream");
