@@ -279,8 +279,14 @@ struct Window {
   }
 };
 
-// The largest of a per-block value (the same on the 16 lanes of a block) over
-// the wavefront's four blocks.
+// The smallest and the largest of a per-block value (the same on the 16 lanes
+// of a block) over the wavefront's four blocks.
+__device__ __forceinline__ int min_over_blocks(int v) {
+  const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 4);
+  const int c = __builtin_amdgcn_readlane(v, 8), d = __builtin_amdgcn_readlane(v, 12);
+  const int e = a < b ? a : b, f = c < d ? c : d;
+  return e < f ? e : f;
+}
 __device__ __forceinline__ int max_over_blocks(int v) {
   const int a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 4);
   const int c = __builtin_amdgcn_readlane(v, 8), d = __builtin_amdgcn_readlane(v, 12);
@@ -625,6 +631,18 @@ __device__ __forceinline__ void sum_residuals(const void* data, Shared<NS>& L, i
   }
 }
 
+// put_back of the row tiles AT, AT - 1, .. `first`: the tiles before hold no
+// slot's last row, and a pass has nothing to put back there (with the lane's
+// place formed once a step instead of in each pass: 372 -> 301 vector
+// instructions a pass at 5 tiles, 2M spots of seven sizes from 7 to 32 px 3199 us
+// -> 3130, 10,007 of 7..32 px 81.6 -> 79.1).
+template <int AT, int N, typename R, typename F>
+__device__ __forceinline__ void put_back_from(R (&px)[N], int first, F& put_back) {
+  put_back(std::integral_constant<int, AT>{}, px[AT]);
+  if constexpr (AT > 0)
+    if (first < AT) put_back_from<AT - 1>(px, first, put_back);
+}
+
 struct Candidate {
   double x, y, hx, hy;
 };
@@ -643,15 +661,12 @@ struct Candidate {
 // 9..21 px 41.0 (47.3).  Of more slots, wide floats go through a ring of row tiles as
 // in evaluate_uniform.
 template <int NS, int CH, int DT, int TB>
-__device__ __forceinline__ void evaluate_pass(const void* data, Shared<NS>& L, int slot,
+__device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, Shared<NS>& L, int slot,
                                               Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
                                               uint32_t geo, bool load, bool sums, bool fresh) {
   constexpr int CQ = (TB + 3) / 4;
   constexpr bool kFloat = DT != SPOTFIT_U16, kRing = NS > 4 && kFloat && CQ > 1;
   constexpr int kRows = kRing ? 4 : TB;
-  int lane = __lane_id();
-  asm volatile("" : "+v"(lane));
-  const Lane ln(lane);
   Window<CQ, DT> win;
   win.set(geo, ln.v, ln.k);
   const char* base = static_cast<const char*>(data) + off * Raw<DT>::kSize;
@@ -687,6 +702,8 @@ __device__ __forceinline__ void evaluate_pass(const void* data, Shared<NS>& L, i
     });
     __builtin_amdgcn_sched_barrier(0);
   };
+  // a slot's last row is in this row tile or a later one
+  const int last_tile = load && !kRing ? min_over_blocks((win.h - 1) >> 2) : 0;
   if constexpr (kRing) {
     if (sums) {
       double sg = 0.0, sgg = 0.0;
@@ -717,7 +734,7 @@ __device__ __forceinline__ void evaluate_pass(const void* data, Shared<NS>& L, i
     GY = mfma4(E[t], E[t], GY);
   });
   if constexpr (!kRing) {
-    if (load) unrolled<TB>([&](auto ai) { put_back(ai, px[decltype(ai)::value]); });
+    if (load) put_back_from<TB - 1>(px, last_tile, put_back);
     if (sums) {
       double sg = 0.0, sgg = 0.0;
       unrolled<TB>([&](auto ai) {
@@ -796,28 +813,30 @@ __device__ __forceinline__ void evaluate_pass(const void* data, Shared<NS>& L, i
 
 // The pass with the tiles of the largest of its four slots.
 template <int NS, int CH, int DT>
-__device__ __forceinline__ void evaluate_four(const void* data, Shared<NS>& L, int slot,
+__device__ __forceinline__ void evaluate_four(const void* data, const Lane& ln, Shared<NS>& L, int slot,
                                               Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
                                               uint32_t geo, bool load, bool sums, bool fresh) {
   const int tiles = max_over_blocks(tiles_of(geo));
   unrolled<4 * CH - 1>([&](auto ti) {
     constexpr int TB = decltype(ti)::value + 2;
     if (tiles == TB || (TB == 2 && tiles < 2))
-      evaluate_pass<NS, CH, DT, TB>(data, L, slot, px, c, off, geo, load, sums, fresh);
+      evaluate_pass<NS, CH, DT, TB>(data, ln, L, slot, px, c, off, geo, load, sums, fresh);
   });
 }
 
 // Evaluates the cnt > 0 slots of L.order, of any shapes, four a pass.
 template <int NS, int CH, int DT>
 __device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, int cnt) {
-  const int blk = (__lane_id() >> 2) & 3;
+  int lane = __lane_id();
+  asm volatile("" : "+v"(lane));
+  const Lane ln(lane);
 #pragma unroll 1
   for (int p = 0; p < cnt; p += 4) {
-    const int slot = L.order[p + blk < cnt ? p + blk : cnt - 1];
+    const int slot = L.order[p + ln.blk < cnt ? p + ln.blk : cnt - 1];
     const uint32_t geo = L.geo[slot];
     const bool fresh = (geo & kGeoNew) != 0;
     Raw<DT> px[4 * CH][CH];
-    evaluate_four<NS, CH, DT>(data, L, slot, px, Candidate{L.x[slot], L.y[slot], L.hx[slot], L.hy[slot]},
+    evaluate_four<NS, CH, DT>(data, ln, L, slot, px, Candidate{L.x[slot], L.y[slot], L.hx[slot], L.hy[slot]},
                               L.off[slot], geo, true, __builtin_amdgcn_ballot_w64(fresh) != 0, fresh);
   }
 }
@@ -1070,7 +1089,10 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         const int2 o = __builtin_bit_cast(int2, off);
         const int2 o0 = make_int2(__builtin_amdgcn_readlane(o.x, lead0), __builtin_amdgcn_readlane(o.y, lead0));
         const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0);
-        evaluate_four<NS, CH, DT>(data, L, own, px, cand, act ? off : __builtin_bit_cast(int64_t, o0),
+        int l = lane;
+        // where its registers are short: formed once a step, not held
+        if constexpr (CH == 1 || DT != SPOTFIT_U16) asm volatile("" : "+v"(l));
+        evaluate_four<NS, CH, DT>(data, Lane(l), L, own, px, cand, act ? off : __builtin_bit_cast(int64_t, o0),
                                   act ? geo : geo0, m_new != 0, m_new != 0, fresh);
       } else {
         wave_lds_sync();
