@@ -36,18 +36,24 @@
 //
 // What bounds it: the vector pipe, which the double-precision matrix
 // instructions share (a 4x4x4_4b issues every 16 cycles and no vector
-// instruction beside it, measured), and, with few wavefronts, the 8 cycles
-// between two vector instructions of one wavefront.  One pass is ~200 vector
-// and 28 matrix instructions at 16x16 px, against ~270 for the same four spots
-// in the lane-owned mapping, whose rows each cost broadcasts, weights and
-// totals beside their two multiply-adds per pixel; at 32x32 px ~400 and 88
-// against ~1050.  Measured on one MI355X against the lane-owned, narrow and
+// instruction beside it, measured), and, with few wavefronts, the chain of one
+// wavefront's own instructions (4.8 cycles each alone, measured).  One pass over
+// spots of one shape is 144 vector and 28 matrix instructions at 16x16 px,
+// against ~270 for the same four spots in the lane-owned mapping, whose rows each
+// cost broadcasts, weights and totals beside their two multiply-adds per pixel;
+// at 32x32 px 375 and 88 against ~1050.  With 64 slots the scalar part is a
+// quarter of a step.  Measured on one MI355X against the lane-owned, narrow and
 // wide mappings these launches took before: 1M spots of 15x15 0.860 ms (1.037),
-// 500k of 32x32 1.41 (2.14), 2M of 7..32 px in one launch 3.20 (4.60), 200,000
-// floats of 17x17 0.584 (0.885), 10,000 of 21x21 0.069 (0.168), 10,007 of 7..32
-// px 0.082 (0.591), 1,024 of 11x11 0.0184 (0.0509).  Passes of mixed shapes in
-// straight-line code for their largest spot's tiles, ordered by size, against a
-// branch per tile in the order of the slots: 3.20 (3.47) and 0.082 (0.110).
+// 500k of 32x32 1.41 (2.14), 2M of seven sizes from 7 to 32 px in one launch 3.13
+// (4.60), 200,000 floats of 17x17 0.584 (0.885), 10,000 of 21x21 0.069 (0.168),
+// 10,007 of 7..32 px 0.079 (0.589), 1,024 of 11x11 0.0179 (0.0480).  Passes of
+// mixed shapes in straight-line code for their largest spot's tiles, ordered by
+// size, against a branch per tile in the order of the slots: 3.20 (3.47) and
+// 0.082 (0.110).  Not faster: the next pass's pixels loaded ahead in passes of
+// mixed shapes (3.34), 44 or 48 slots at three wavefronts per SIMD (15x15 0.877,
+// 0.917), the sums of g and g^2 taken from the products of a new spot's first
+// pass (0.870), a solve of three rows for wavefronts without elliptical spots
+// (no case moved by more than its runs differ).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -129,7 +135,7 @@ struct Shared {
   int order[NS];     // the slots to evaluate, new spots first
   double p10[2 * kP10 + 1];
   // normal equations at the best point (of 4 slots: before the contraction of a
-  // symmetric spot), for a retry with more damping; a wavefront of 64 slots
+  // symmetric spot), for a retry with more damping; a wavefront of more slots
   // evaluates the best point again instead
   static constexpr bool kKeepA = NS <= 16;
   double A[kKeepA ? 14 : 1][kKeepA ? NS : 1];
@@ -824,6 +830,58 @@ __device__ __forceinline__ void evaluate_four(const void* data, const Lane& ln, 
   });
 }
 
+// chi^2 summed over the pixels (Eq. 2) of a wavefront of 4 slots, 16-bit data, on
+// every lane of a block: of its slot (shape geo) at c, with the pixels that its
+// lanes hold.  As sum_residuals, which reads the pixels again and takes its sums
+// through LDS: with few spots a launch is as long as its longest chain of steps
+// (4,000 raw spots of 9..21 px 38.9 us -> 37.5, one served frame of 110 63.4 ->
+// 61.0, 1,024 of 11x11 18.3 -> 17.9).
+template <int CH, int DT, int TB>
+__device__ __forceinline__ double block_residuals_of(const Lane& ln, const Raw<DT> (&px)[4 * CH][CH],
+                                                     const Candidate& c, uint32_t geo, double alpha,
+                                                     double beta) {
+  constexpr int CQ = (TB + 3) / 4;
+  Window<CQ, DT> win;
+  win.set(geo, ln.v, ln.k);
+  double exq[CQ], eyq[CQ], c2s = 0.0;
+  unrolled<CQ>([&](auto qi) {
+    constexpr int q = decltype(qi)::value;
+    factors<q>(ln, win, c.x, c.y, c.hx, c.hy, exq[q], eyq[q]);
+  });
+  unrolled<CQ>([&](auto qi) {
+    constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
+    double aex[4], cs[4];
+    unrolled<B>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      aex[t] = alpha * lg::gbcast<4, t>(exq[q]);
+      cs[t] = 0.0;
+    });
+    unrolled<TB>([&](auto ai) {
+      constexpr int at = decltype(ai)::value;
+      residual_row<at, B>(ln, px[at][q].fresh(), aex, eyq[at / 4], beta, win.h, cs);
+    });
+    unrolled<B>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      c2s += t < win.own[q] ? cs[t] : 0.0;
+    });
+  });
+  return block_sum(c2s);
+}
+template <int CH, int DT>
+__device__ __forceinline__ double block_residuals(const Raw<DT> (&px)[4 * CH][CH], const Candidate& c,
+                                                  uint32_t geo, double alpha, double beta) {
+  int lane = __lane_id();
+  asm volatile("" : "+v"(lane));
+  const Lane ln(lane);
+  const int tiles = max_over_blocks(tiles_of(geo));
+  double c2 = 0.0;
+  unrolled<4 * CH - 1>([&](auto ti) {
+    constexpr int TB = decltype(ti)::value + 2;
+    if (tiles == TB || (TB == 2 && tiles < 2)) c2 = block_residuals_of<CH, DT, TB>(ln, px, c, geo, alpha, beta);
+  });
+  return c2;
+}
+
 // Evaluates the cnt > 0 slots of L.order, of any shapes, four a pass.
 template <int NS, int CH, int DT>
 __device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, int cnt) {
@@ -1172,7 +1230,32 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         chi = L.tot[kChi][own];
       }
     }
-    if constexpr (DT == SPOTFIT_U16) {
+    if constexpr (DT == SPOTFIT_U16 && kBlocks) {
+      bool want = near_self || near_best;
+      bool of_best = false;  // first the candidates' sums, then the best points'
+#pragma unroll 1
+      while (__builtin_amdgcn_ballot_w64(want) != 0) {
+        Candidate at = cand;
+        double alpha = am.a, beta = am.b;
+        if (of_best) {
+          at = Candidate{best[0], best[1], -0.5 * rcp_nr(best[2] * best[2]), -0.5 * rcp_nr(best[3] * best[3])};
+          alpha = a_best;
+          beta = b_best;
+        }
+        const double c2 = block_residuals<CH, DT>(px, at, geo, alpha, beta);
+        if (want) {
+          if (of_best) {
+            chi_best = c2;
+            chib_err = 0.0;
+          } else {
+            chi = c2;
+            chi_err = 0.0;
+          }
+        }
+        want = !of_best && near_best && chib_err > 0.0;
+        of_best = true;
+      }
+    } else if constexpr (DT == SPOTFIT_U16) {
       bool want = near_self || near_best;
       if (__builtin_amdgcn_ballot_w64(want) != 0) {
         bool of_best = false;  // first the candidates' sums, then the best points'
@@ -1190,13 +1273,6 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
               L.y[own] = best[1];
               L.hx[own] = -0.5 * rcp_nr(best[2] * best[2]);
               L.hy[own] = -0.5 * rcp_nr(best[3] * best[3]);
-            } else if constexpr (kBlocks) {
-              L.x[own] = cand.x;
-              L.y[own] = cand.y;
-              L.hx[own] = cand.hx;
-              L.hy[own] = cand.hy;
-              L.off[own] = off;
-              L.geo[own] = geo;
             }
           }
           wave_lds_sync();
