@@ -95,7 +95,7 @@ __device__ const double kPow10[2 * kP10 + 1] = {
 // The spots of a launch.  Position p is spot p, or, with the class lists of a
 // mixed-size batch, entry p of the lists from the largest class down.  A launch
 // that holds every spot at once (take null) gives wavefront b the positions
-// NS b .. NS b + NS - 1.  Otherwise the positions go out in chunks of C from
+// per b .. per b + per - 1.  Otherwise the positions go out in chunks of C from
 // kMatrixCounters counters, wavefront b drawing from counter b % kMatrixCounters:
 // atomics on one address from all over the chip pass one by one (about 50 ns
 // each), so one counter for 2,000 wavefronts held up 1M spots of 15x15 px by
@@ -108,6 +108,7 @@ struct MatrixQueue {
   int64_t cap;
   int32_t* take;
   int32_t count, first;  // positions; chunks per counter given out at the start
+  int32_t per;           // positions of a wavefront that takes no more
   __device__ __forceinline__ int32_t spot(int32_t p) const {
     if ((uint32_t)p >= (uint32_t)count) return -1;
     if (!counts) return p;
@@ -1126,7 +1127,8 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
   {
     Next nx;
     const int wave = blockIdx.x / kMatrixCounters;
-    if (owner) look_up(left ? position(wave * (NS / C), own) : (int32_t)(blockIdx.x * NS + own), nx);
+    if (owner)
+      look_up(left ? position(wave * (NS / C), own) : own < mq.per ? (int32_t)blockIdx.x * mq.per + own : -1, nx);
     if (lane < 2 * kP10 + 1) L.p10[lane] = kPow10[lane];
     if (s >= 0) begin(nx);
   }
@@ -1516,7 +1518,7 @@ const void* matrix_kernel_symbol(int slots, bool wide, int dtype) {
 }
 
 hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const MixedWs* ws, int resident,
-                                hipStream_t st) {
+                                int spread, hipStream_t st) {
   const int64_t need = (ka.n + slots - 1) / slots;
   int grid = (int)(need < resident ? need : resident);
   mtx::MatrixQueue mq{};
@@ -1534,7 +1536,16 @@ hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const Mix
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   } else {
-    grid = (int)need;
+    // of 4 slots and spots of several shapes, as few spots per wavefront as come
+    // with `spread` wavefronts: a small spot's steps then don't wait for a large
+    // one's tiles, nor either for the other's close decisions (a frame of 110
+    // spots of 9..21 px with a wavefront per spot 57.0 us, with four spots each
+    // 61.0; of one shape it does not pay: 32 spots of 13x13 31.3 and 30.5, 1,024
+    // of 11x11 19.3 and 17.9)
+    mq.per = slots;
+    if (slots == 4 && spread > 0)
+      for (mq.per = 1; mq.per < 4 && (ka.n + mq.per - 1) / mq.per > spread;) mq.per *= 2;
+    grid = (int)((ka.n + mq.per - 1) / mq.per);
   }
 #define SF_MXLAUNCH(NS, CH) \
   if (slots == NS && wide == (CH == 2)) return mtx::launch<NS, CH>(ka, mq, grid, st);

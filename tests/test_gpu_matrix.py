@@ -127,3 +127,12 @@ def test_batch_sizes_of_every_build(n):
     big = spotgen.SpotBatch(b.data, b.sizes[t], b.offsets[t], b.init[t], b.truth, "tiled")
     ref = _fit(b, 4, schedule=1)
     _equal(_fit(big, schedule=1), {k: v[t] for k, v in ref.items()})
+
+
+@pytest.mark.parametrize("n", [1, 3, 256, 257, 512, 513, 1025])
+def test_small_mixed_batches_spread_over_the_chip(n):
+    """One, two and four spots per wavefront of the build for four (the last
+    wavefront part full): the bits of the same spots in one larger batch."""
+    _, b, _ = _shapes([(5, 7), (9, 9), (17, 12), (24, 31)], 300)
+    ref = _fit(b, 16, schedule=1)
+    _equal(_fit(b.subset(np.arange(n)), schedule=1), {k: v[:n] for k, v in ref.items()})
