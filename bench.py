@@ -288,7 +288,7 @@ def main():
     if cnt is not None:
         simd_cycles = 256 * 4 * CLOCK_HZ * k_avg_s
         f64 = cnt["SQ_INSTS_VALU_FMA_F64"] * 2 + cnt["SQ_INSTS_VALU_MUL_F64"] + \
-            cnt["SQ_INSTS_VALU_ADD_F64"]
+            cnt["SQ_INSTS_VALU_ADD_F64"] + 8 * cnt.get("SQ_INSTS_MFMA", 0)  # 512 flop each, per lane
         valu = {"issue_frac": cnt["SQ_INSTS_VALU"] * 4 / simd_cycles,
                 "fp64_flop_frac": f64 * 64 / k_avg_s / (PEAK_ALU_TFLOPS * 1e12),
                 "valu_insts_per_launch": cnt["SQ_INSTS_VALU"],

@@ -363,8 +363,8 @@ class Context:
     def fit_raw(self, data, sizes, offsets, opts: Optional[Options] = None, out=None,
                 want_evals: bool = False, stream=None):
         """Raw spots in, fits out (spotfit_fit_raw): the centroid / second-moment start
-        values and the fit from them, in the fit's own launch with the double-precision
-        kernels.  Returns fit_spots' outputs plus "init", float32 [n, 4]: the start
+        values, then the fit from them (a launch each on the default plan).  Returns
+        fit_spots' outputs plus "init", float32 [n, 4]: the start
         values each fit began from.  `out` may supply any of the outputs, "init" too."""
         import torch
         n = int(sizes.shape[0])
