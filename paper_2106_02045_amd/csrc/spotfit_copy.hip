@@ -71,18 +71,20 @@ hipError_t launch_copy(const CopyList& l, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The device's address of n bytes of pinned host memory, or null when they are
-// not all pinned.
+// The device's address of n bytes of pinned host memory, or null when they do not
+// lie in one pinned allocation.  (Two ends that are pinned say nothing about what
+// is between them: a device address is the host's own.)
 void* pinned_address(const void* host, int64_t n) {
-  hipPointerAttribute_t a, b;
-  const char* last = static_cast<const char*>(host) + (n - 1);
-  if (hipPointerGetAttributes(&a, host) != hipSuccess || hipPointerGetAttributes(&b, last) != hipSuccess) {
+  hipPointerAttribute_t a;
+  hipDeviceptr_t base = nullptr;
+  size_t size = 0;
+  if (n <= 0 || hipPointerGetAttributes(&a, host) != hipSuccess ||
+      hipMemGetAddressRange(&base, &size, const_cast<void*>(host)) != hipSuccess) {
     (void)hipGetLastError();  // an address the runtime does not know
     return nullptr;
   }
-  if (a.type != hipMemoryTypeHost || b.type != hipMemoryTypeHost || !a.devicePointer ||
-      static_cast<char*>(b.devicePointer) - static_cast<char*>(a.devicePointer) != n - 1)
-    return nullptr;
+  const uintptr_t from = reinterpret_cast<uintptr_t>(host) - reinterpret_cast<uintptr_t>(base);
+  if (a.type != hipMemoryTypeHost || !a.devicePointer || from > size || (size_t)n > size - from) return nullptr;
   return a.devicePointer;
 }
 
