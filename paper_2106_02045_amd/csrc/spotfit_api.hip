@@ -416,6 +416,16 @@ int check_call(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
   return SPOTFIT_OK;
 }
 
+// The mixed schedule's spot indices are 32-bit: a larger batch is refused as
+// spotfit_ctx_reserve refuses its workspace, whether or not this batch would go
+// through it.
+int check_mixed_count(const spotfit_options_t& o, int64_t n, const char* who) {
+  if (o.precision == SPOTFIT_PREC_FP64 && o.schedule == SPOTFIT_SCHEDULE_MIXED &&
+      n > ((int64_t)1 << 31) - 1)
+    return fail(SPOTFIT_E_ARG, std::string(who) + ": a mixed-schedule call takes fewer than 2^31 spots");
+  return SPOTFIT_OK;
+}
+
 // Largest batch for which the latency hint takes the one-wave-per-SIMD build
 // of the wide mixed-size plan (measured: faster up to 40,000 spots of the
 // serving and mixed workloads, slower from 400,000).
@@ -720,6 +730,7 @@ int spotfit_fit_spots(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   spotfit_options_t o;
   int rc = check_call(ctx, data, dtype, sizes, offsets, init, n, opt, params_out, chi2_out,
                       iters_out, status_out, &o, "fit_spots");
+  if (rc == SPOTFIT_OK) rc = check_mixed_count(o, n, "fit_spots");
   if (rc != SPOTFIT_OK || n == 0) return rc;
   return launch_fit(ctx, data, dtype, sizes, offsets, init, n, o, params_out, chi2_out, iters_out,
                     status_out, evals_out, stream);
@@ -756,6 +767,7 @@ int spotfit_fit_raw(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   spotfit_options_t o;
   int rc = check_call(ctx, data, dtype, sizes, offsets, init_out, n, opt, params_out, chi2_out,
                       iters_out, status_out, &o, "fit_raw");
+  if (rc == SPOTFIT_OK) rc = check_mixed_count(o, n, "fit_raw");
   if (rc != SPOTFIT_OK || n == 0) return rc;
   return launch_raw(ctx, data, dtype, sizes, offsets, n, o, init_out, params_out, chi2_out,
                     iters_out, status_out, evals_out, stream);
@@ -838,6 +850,7 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   spotfit_options_t o;
   int rc = check_call(ctx, data, dtype, sizes, offsets, init, n, opt, params_out, chi2_out,
                       iters_out, status_out, &o, "autotune");
+  if (rc == SPOTFIT_OK) rc = check_mixed_count(o, n, "autotune");
   if (rc != SPOTFIT_OK) return rc;
   if (o.precision != SPOTFIT_PREC_FP64)
     return fail(SPOTFIT_E_OPTIONS, "autotune: only the double-precision separable kernel has plans");
