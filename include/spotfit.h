@@ -302,7 +302,9 @@ typedef struct {
  * opt->max_side; for the mixed schedule, the mixed-size plans.  Each plan gets
  * one warm-up call and `reps` (>= 1) timed calls on `stream`, which the call
  * waits for; the fastest is kept in the context for later calls with that
- * schedule and size class.  The output arrays hold the last call's results.
+ * schedule and size class.  Calls with SPOTFIT_PLAN_LATENCY have one mapping: with
+ * that hint it alone is timed, and what the context keeps does not change.  The
+ * output arrays hold the last call's results.
  * All plans take the same decisions on every spot, but their sums run in
  * different orders, so results can differ in the last bits between plans: a
  * context is bitwise reproducible between tunings.  report may be NULL.

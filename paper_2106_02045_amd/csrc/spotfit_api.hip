@@ -861,7 +861,11 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   const int side = cls == 0 ? 8 : cls == 1 ? 16 : 32;
   int cand[16];
   int nc = 0;
-  if (mixed) {
+  if (o.plan_hint == SPOTFIT_PLAN_LATENCY) {
+    // the hint's calls run one kernel whatever the context keeps (takes_matrix):
+    // there is nothing to choose, and what throughput calls take stays as it is
+    cand[nc++] = mixed ? matrix_mixed_plan() : matrix_plan();
+  } else if (mixed) {
     cand[nc++] = matrix_mixed_plan();
     for (int p = 0; p < sf::mixed_plan_count() && nc < 16; ++p) cand[nc++] = p;
   } else {
@@ -901,7 +905,7 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
-  const int chosen = rc == SPOTFIT_OK ? cand[best] : keep;
+  const int chosen = rc == SPOTFIT_OK && o.plan_hint != SPOTFIT_PLAN_LATENCY ? cand[best] : keep;
   if (mixed)
     ctx->mixed_plan = chosen;
   else
