@@ -288,7 +288,8 @@ int spotfit_get_stats(spotfit_ctx_t* ctx, const int32_t* status, const int32_t* 
 typedef struct {
   int32_t schedule;      /* spotfit_schedule_t that was tuned                       */
   int32_t size_class;    /* uniform: 0 (max_side <= 8), 1 (<= 16), 2 (<= 32); mixed: -1 */
-  int32_t n_candidates;  /* entries used in plan_id / plan_ms                        */
+  int32_t n_candidates;  /* entries used in plan_id / plan_ms; of more than 16 timed
+                            plans the 16 fastest                                     */
   int32_t chosen;        /* index of the kept plan in plan_id                        */
   int32_t plan_id[16];   /* internal plan numbers (the SPOTFIT_GROUP_PLAN /
                             SPOTFIT_MIXED_PLAN override values)                      */

@@ -859,7 +859,9 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
   const bool mixed = o.schedule == SPOTFIT_SCHEDULE_MIXED;
   const int cls = o.max_side <= 8 ? 0 : o.max_side <= 16 ? 1 : 2;
   const int side = cls == 0 ? 8 : cls == 1 ? 16 : 32;
-  int cand[16];
+  constexpr int kMaxPlans = 24;  // at least the plans there are
+  constexpr int kReported = 16;  // entries of the report
+  int cand[kMaxPlans];
   int nc = 0;
   if (o.plan_hint == SPOTFIT_PLAN_LATENCY) {
     // the hint's calls run one kernel whatever the context keeps (takes_matrix):
@@ -867,16 +869,16 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
     cand[nc++] = mixed ? matrix_mixed_plan() : matrix_plan();
   } else if (mixed) {
     cand[nc++] = matrix_mixed_plan();
-    for (int p = 0; p < sf::mixed_plan_count() && nc < 16; ++p) cand[nc++] = p;
+    for (int p = 0; p < sf::mixed_plan_count() && nc < kMaxPlans; ++p) cand[nc++] = p;
   } else {
     cand[nc++] = matrix_plan();
-    for (int p = 0; p < sf::group_plan_count() && nc < 16; ++p) {
+    for (int p = 0; p < sf::group_plan_count() && nc < kMaxPlans; ++p) {
       int L = 0, C = 0;
       sf::group_plan_shape(p, &L, &C);
       if (L * C >= side) cand[nc++] = p;
     }
   }
-  double ms[16];
+  double ms[kMaxPlans];
   hipStream_t st = (hipStream_t)stream;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t e = hipEventCreate(&e0);
@@ -916,8 +918,20 @@ int spotfit_autotune(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
                   status_out, nullptr, stream);
   if (rc != SPOTFIT_OK) return rc;
   if ((e = hipStreamSynchronize(st)) != hipSuccess) return fail_hip(e, "hipStreamSynchronize");
+  while (nc > kReported) {  // the slowest stay out of the report
+    int worst = 0;
+    for (int i = 1; i < nc; ++i)
+      if (ms[i] > ms[worst]) worst = i;
+    --nc;
+    if (best > worst) --best;
+    for (int i = worst; i < nc; ++i) {
+      cand[i] = cand[i + 1];
+      ms[i] = ms[i + 1];
+    }
+  }
   if (report) {
     std::memset(report, 0, sizeof *report);
+    static_assert(sizeof report->plan_id / sizeof report->plan_id[0] == kReported, "entries of the report");
     report->schedule = o.schedule;
     report->size_class = mixed ? -1 : cls;
     report->n_candidates = nc;
