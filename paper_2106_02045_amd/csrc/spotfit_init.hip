@@ -13,6 +13,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "lanegroup.h"
 #include "spotfit.h"
 #include "spotfit_internal.h"
@@ -59,26 +61,26 @@ constexpr double kPi = 0x1.921fb54442d18p+1;
 // ---------------------------------------------------------------------------
 
 // A row as read: windows of 4 pixels, each two registers; zeros past column w.
-template <int L>
+template <int W>
 struct Row {
-  uint32_t v[L / 2];
+  uint32_t v[2 * W];
 };
 
 // Row r of a spot (zeros for r >= h).  A window that would read past the spot's
 // end starts earlier; its pixels and the end of the row are shifted into place.
-template <int L>
-__device__ __forceinline__ void load_row(const uint16_t* px, int w, int h, int r, Row<L>& row) {
+template <int W>
+__device__ __forceinline__ void load_row(const uint16_t* px, int w, int h, int r, Row<W>& row) {
   typedef uint32_t vec __attribute__((ext_vector_type(2), aligned(2)));
   const int n = w * h, cols = r < h ? w : 0, first = r < h ? r * w : 0;
-  uint64_t t[L / 4];
+  uint64_t t[W];
 #pragma unroll
-  for (int q = 0; q < L / 4; ++q) {
+  for (int q = 0; q < W; ++q) {
     const int p = first + 4 * q < n - 4 ? first + 4 * q : n - 4;
     const vec u = *reinterpret_cast<const vec*>(px + p);
     t[q] = (uint64_t)u[1] << 32 | u[0];
   }
 #pragma unroll
-  for (int q = 0; q < L / 4; ++q) {
+  for (int q = 0; q < W; ++q) {
     int keep = cols - 4 * q;  // pixels of the row in this window
     keep = keep > 4 ? 4 : keep;
     const int p = first + 4 * q < n - 4 ? first + 4 * q : n - 4;
@@ -168,15 +170,88 @@ __device__ __forceinline__ void ring_middle(const uint16_t* px, int w, int h, in
   v2 = le >= k1 + 2 ? v : above;
 }
 
-// The spots of a wavefront, their descriptions one per lane.
+// The spots of a wavefront, up to 64 from `base` on, their descriptions one per
+// lane, and the usable ones in the order in which they are gone through: by the
+// lanes that their larger side takes (8, 16 or 32), whatever sides the launch is
+// for.  100,000 spots of 9x9 with the default options (sides up to 32): moments 45.8
+// us with groups of 16 lanes and two columns each, 57.6 with 32 lanes for every
+// spot, 23.2 so; brightest-pixel values 24.3, 74.6 and 20.6 (of 7..16 px 20.8 instead
+// of 75; of 17..32 px as before).
 struct Batch {
   spotfit_shape_t sh;  // of spot `base + lane`
   int64_t off;
   bool ok;
-  int count;
+  int first[4];  // class c (8 << c lanes) is order[first[c]] .. order[first[c + 1] - 1]
 };
 
+// Fills the batch for a kernel of up to LMAX lanes per spot; order: 64 words of LDS.
+template <int LMAX>
+__device__ __forceinline__ Batch take_batch(const spotfit_shape_t* sizes, const int64_t* offsets, int64_t base,
+                                            int count, int max_side, int max_pixels, int* order) {
+  const int lane = __lane_id();
+  Batch b{};
+  if (lane < count) {
+    b.sh = sizes[base + lane];
+    b.off = offsets[base + lane];
+  }
+  b.ok = lane < count && usable<LMAX>(b.sh, max_side, max_pixels);
+  const int side = b.sh.w > b.sh.h ? b.sh.w : b.sh.h;
+  uint64_t m[3];  // the lanes of each class
+  m[0] = __builtin_amdgcn_ballot_w64(b.ok && side <= 8);
+  m[1] = __builtin_amdgcn_ballot_w64(b.ok && side > 8 && side <= 16);
+  m[2] = __builtin_amdgcn_ballot_w64(b.ok && side > 16);
+  // a few small spots among larger ones go along with those where that takes no
+  // more rounds
+#pragma unroll
+  for (int c = 0; c < 2; ++c) {
+    if ((16 << c) > LMAX) continue;
+    const int some = __builtin_popcountll(m[c]), more = __builtin_popcountll(m[c + 1]), G = 4 >> c;
+    if ((some + more + G - 1) / G <= (some + 2 * G - 1) / (2 * G) + (more + G - 1) / G) {
+      m[c + 1] |= m[c];
+      m[c] = 0;
+    }
+  }
+#pragma unroll
+  for (int c = 0; c < 3; ++c) {
+    if (m[c] >> lane & 1)
+      order[b.first[c] + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32),
+                                                        __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], 0u))] = lane;
+    b.first[c + 1] = b.first[c] + (int)__builtin_popcountll(m[c]);
+  }
+  __syncthreads();
+  return b;
+}
+
 __device__ __forceinline__ int pick(int v, int lane) { return __builtin_amdgcn_ds_bpermute(lane << 2, v); }
+
+// f(windows, from, valid, w, h, pixels) for the spots of the batch that take L
+// lanes, 64 / L at a time: `from` the lane that describes the spot of this lane's
+// group (the last one again where there are no more: not valid).  Rows are gone
+// through in L / 4 windows of 4 columns; with 32 lanes in 6 where no spot has more
+// than 24 columns, 58 us instead of 75 for the brightest-pixel values of
+// 100,000 spots of 17x17.
+template <int L, typename F>
+__device__ __forceinline__ void for_spots(const Batch& b, const uint16_t* data, const int* order, F&& f) {
+  constexpr int C = L == 8 ? 0 : L == 16 ? 1 : 2, G = 64 / L;
+  const int begin = b.first[C], end = b.first[C + 1];
+  if (begin == end) return;
+  const int g = __lane_id() / L;
+  const int2 o2 = __builtin_bit_cast(int2, b.off);
+  const int whs = b.sh.w | b.sh.h << 8;
+  auto go = [&](auto windows) {
+#pragma unroll 1
+    for (int i = begin; i < end; i += G) {
+      const int from = order[i + g < end ? i + g : end - 1];
+      const int wh = pick(whs, from);
+      const int64_t o = __builtin_bit_cast(int64_t, make_int2(pick(o2.x, from), pick(o2.y, from)));
+      f(windows, from, i + g < end, wh & 0xff, wh >> 8, data + o);
+    }
+  };
+  if constexpr (L == 32) {
+    if (__builtin_amdgcn_ballot_w64(b.ok && b.sh.w > 24) == 0) return go(std::integral_constant<int, 6>{});
+  }
+  go(std::integral_constant<int, L / 4>{});
+}
 
 // Start values from the moments of max(g - b0, 0), b0 the mean of the ring's
 // middle values v1, v2: 2 max(g - b0, 0) = max(g - floor b0, 0) + max(g - ceil
@@ -185,63 +260,55 @@ __device__ __forceinline__ int pick(int v, int lane) { return __builtin_amdgcn_d
 // value of its own and four lanes repeating the spot's last steps: 1M spots of
 // 15x15 in 0.196 ms instead of 0.50, of 32x32 in 0.60 instead of 1.19.
 template <int L>
+__device__ __forceinline__ void moment_rows(const Batch& b, const uint16_t* data, const int* order, double* sxx,
+                                            double* syy, uint32_t* s0, uint32_t* sx, uint32_t* sy) {
+  const int r = __lane_id() % L;
+  for_spots<L>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
+    constexpr int W = decltype(windows)::value;
+    Row<W> row;
+    load_row<W>(px, w, h, r, row);
+    uint32_t v1, v2;
+    ring_middle<L>(px, w, h, r, row.v[0] & 0xffffu, v1, v2);
+    const uint32_t k0 = (v1 + v2) >> 1, k1 = (v1 + v2 + 1) >> 1;
+    const uint32_t b0 = k0 | k0 << 16, b1 = k1 | k1 << 16;
+    uint32_t a0 = 0, a1 = 0, a2 = 0;  // the row's sums of 2 wt, 2 wt c, 2 wt c^2 (below 2^31)
+#pragma unroll
+    for (int p = 0; p < 2 * W; ++p) {
+      const uint32_t c = 2 * p, one = 0x10001u, lin = c | (c + 1) << 16, sq = c * c | (c + 1) * (c + 1) << 16;
+      const uint32_t d = sub_sat(row.v[p], b0), e = sub_sat(row.v[p], b1);
+      a0 = dot2(e, one, dot2(d, one, a0));
+      a1 = dot2(e, lin, dot2(d, lin, a1));
+      a2 = dot2(e, sq, dot2(d, sq, a2));
+    }
+    const double yy = gsum<L>(double(a0) * double(r * r)), xx = gsum<L>(double(a2));
+    const uint32_t t0 = (uint32_t)gsum_i<L>((int)a0), t1 = (uint32_t)gsum_i<L>((int)a1);
+    const uint32_t ty = (uint32_t)gsum_i<L>((int)(a0 * (uint32_t)r));
+    if (r == 0 && valid) {
+      sxx[from] = xx;
+      syy[from] = yy;
+      s0[from] = t0;
+      sx[from] = t1;
+      sy[from] = ty;
+    }
+  });
+}
+
+template <int LMAX>
 __global__ __launch_bounds__(64) void moment_rows_kernel(const uint16_t* data, const spotfit_shape_t* sizes,
                                                          const int64_t* offsets, int64_t n, int per_block,
                                                          int max_side, int max_pixels, float* out) {
-  constexpr int G = 64 / L;
   __shared__ double sxx[64], syy[64];
   __shared__ uint32_t s0[64], sx[64], sy[64];
-  const int lane = __lane_id(), r = lane % L, g = lane / L;
+  __shared__ int order[64];
+  const int lane = __lane_id();
   const int64_t base = (int64_t)blockIdx.x * per_block;
   const int count = n - base < per_block ? (int)(n - base) : per_block;
-  spotfit_shape_t sh{0, 0, 0, 0};
-  int64_t off = 0;
-  if (lane < count) {
-    sh = sizes[base + lane];
-    off = offsets[base + lane];
-  }
-  const bool ok = lane < count && usable<L>(sh, max_side, max_pixels);
-  // (an unusable spot goes through as 3 x 3 pixels of a usable one, if there is one)
-  const uint64_t m_ok = __builtin_amdgcn_ballot_w64(ok);
-  if (m_ok != 0) {
-    const int some = (int)__builtin_ctzll(m_ok);
-    const int2 o2 = __builtin_bit_cast(int2, off);
-    const int whs = sh.w | sh.h << 8;
-#pragma unroll 1
-    for (int i = 0; i < count; i += G) {
-      const int want = i + g < count ? i + g : count - 1;
-      const int from = (m_ok >> want & 1) ? want : some;
-      const int wh = pick(whs, from);
-      const int w = wh & 0xff, h = wh >> 8;
-      const int64_t o = __builtin_bit_cast(int64_t, make_int2(pick(o2.x, from), pick(o2.y, from)));
-      const uint16_t* px = data + o;
-      Row<L> row;
-      load_row<L>(px, w, h, r, row);
-      uint32_t v1, v2;
-      ring_middle<L>(px, w, h, r, row.v[0] & 0xffffu, v1, v2);
-      const uint32_t k0 = (v1 + v2) >> 1, k1 = (v1 + v2 + 1) >> 1;
-      const uint32_t b0 = k0 | k0 << 16, b1 = k1 | k1 << 16;
-      uint32_t a0 = 0, a1 = 0, a2 = 0;  // the row's sums of 2 wt, 2 wt c, 2 wt c^2 (below 2^31)
-#pragma unroll
-      for (int p = 0; p < L / 2; ++p) {
-        const uint32_t c = 2 * p, one = 0x10001u, lin = c | (c + 1) << 16, sq = c * c | (c + 1) * (c + 1) << 16;
-        const uint32_t d = sub_sat(row.v[p], b0), e = sub_sat(row.v[p], b1);
-        a0 = dot2(e, one, dot2(d, one, a0));
-        a1 = dot2(e, lin, dot2(d, lin, a1));
-        a2 = dot2(e, sq, dot2(d, sq, a2));
-      }
-      const double yy = gsum<L>(double(a0) * double(r * r)), xx = gsum<L>(double(a2));
-      const uint32_t t0 = (uint32_t)gsum_i<L>((int)a0), t1 = (uint32_t)gsum_i<L>((int)a1);
-      const uint32_t ty = (uint32_t)gsum_i<L>((int)(a0 * (uint32_t)r));
-      if (r == 0 && i + g < count) {
-        sxx[i + g] = xx;
-        syy[i + g] = yy;
-        s0[i + g] = t0;
-        sx[i + g] = t1;
-        sy[i + g] = ty;
-      }
-    }
-  }
+  const Batch b = take_batch<LMAX>(sizes, offsets, base, count, max_side, max_pixels, order);
+  const spotfit_shape_t sh = b.sh;
+  const bool ok = b.ok;
+  moment_rows<8>(b, data, order, sxx, syy, s0, sx, sy);
+  if constexpr (LMAX >= 16) moment_rows<16>(b, data, order, sxx, syy, s0, sx, sy);
+  if constexpr (LMAX >= 32) moment_rows<32>(b, data, order, sxx, syy, s0, sx, sy);
   __syncthreads();
   if (lane < count) {
     float o[4];
@@ -272,91 +339,84 @@ __global__ __launch_bounds__(64) void moment_rows_kernel(const uint16_t* data, c
 // its first brightest window.  Measured: 1M spots of 15x15 in 0.188 ms instead
 // of 0.79, of 32x32 in 0.67 instead of 1.50.
 template <int L>
+__device__ __forceinline__ void peak_rows(const Batch& b, const uint16_t* data, const int* order,
+                                          uint32_t* where, uint32_t* area) {
+  const int r = __lane_id() % L;
+  for_spots<L>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
+    constexpr int W = decltype(windows)::value;
+    Row<W> row;
+    load_row<W>(px, w, h, r, row);
+    // 36 / (rows x columns of the window), for inner and for edge columns
+    const bool row_edge = r == 0 || r == h - 1;
+    const uint32_t inner = r < h ? (row_edge ? 6u * 32 : 4u * 32) : 0u;
+    const uint32_t edge = r < h ? (row_edge ? 9u * 32 : 6u * 32) : 0u;
+    uint32_t best = 0, left = 0, mid = row.v[0] & 0xffffu;
+    uint32_t hi2 = 0, lo2 = 0xffffffffu;
+#pragma unroll
+    for (int c = 0; c < 4 * W; ++c) {
+      const uint32_t right = c + 1 < 4 * W ? (c & 1 ? row.v[(c + 1) / 2 < 2 * W ? (c + 1) / 2 : 0] & 0xffffu
+                                                    : row.v[c / 2] >> 16)
+                                           : 0u;
+      const uint32_t across = left + mid + right;
+      uint32_t up, down;
+      if constexpr (L == 16) {  // a group is a DPP row: zeros come in at its ends
+        up = (uint32_t)dpp_i<0x111>((int)across);    // row_shr:1
+        down = (uint32_t)dpp_i<0x101>((int)across);  // row_shl:1
+      } else {
+        up = (uint32_t)dpp_i<0x138>((int)across);    // wave_shr:1
+        down = (uint32_t)dpp_i<0x130>((int)across);  // wave_shl:1
+        up = r == 0 ? 0u : up;
+        down = r == L - 1 ? 0u : down;
+      }
+      const uint32_t mult = c == 0 ? edge : c < w - 1 ? inner : c == w - 1 ? edge : 0u;
+      const uint32_t key = (across + up + down) * mult + uint32_t(31 - c);
+      best = key > best ? key : best;
+      left = mid;
+      mid = right;
+    }
+    // smallest and largest pixel of the row
+#pragma unroll
+    for (int p = 0; p < 2 * W; ++p) {
+      hi2 = max2(hi2, row.v[p]);
+      const uint32_t past = 2 * p >= w ? 0xffffffffu : 2 * p + 1 >= w ? 0xffff0000u : 0u;
+      lo2 = min2(lo2, row.v[p] | past);
+    }
+    uint32_t hi = (hi2 & 0xffffu) > hi2 >> 16 ? hi2 & 0xffffu : hi2 >> 16;
+    uint32_t lo = (lo2 & 0xffffu) < lo2 >> 16 ? lo2 & 0xffffu : lo2 >> 16;
+    lo = r < h ? lo : 0xffffu;
+    hi = gmax_u<L>(hi);
+    lo = gmin_u<L>(lo);
+    // the group's brightest window: the first row among the largest means
+    const uint32_t mean = best >> 5, top = gmax_u<L>(mean);
+    const uint32_t at = gmin_u<L>(mean == top && r < h ? uint32_t(r) << 5 | (31u - (best & 31u)) : 0xffffffffu);
+    const double thr = __builtin_fma(double(hi) - double(lo), kExpMinusHalf, double(lo));
+    // g > thr is g > floor(thr): count max(g - floor(thr), 0) != 0
+    const uint32_t f = (uint32_t)thr, f2 = f | f << 16;
+    uint32_t m = 0;
+#pragma unroll
+    for (int p = 0; p < 2 * W; ++p) m = dot2(min2(sub_sat(row.v[p], f2), 0x10001u), 0x10001u, m);
+    m = (uint32_t)gsum_i<L>((int)m);
+    if (r == 0 && valid) {
+      where[from] = at;
+      area[from] = m;
+    }
+  });
+}
+
+template <int LMAX>
 __global__ __launch_bounds__(64) void peak_rows_kernel(const uint16_t* data, const spotfit_shape_t* sizes,
                                                        const int64_t* offsets, int64_t n, int per_block,
                                                        int max_side, int max_pixels, float* out) {
-  constexpr int G = 64 / L;
   __shared__ uint32_t where[64], area[64];
-  const int lane = __lane_id(), r = lane % L, g = lane / L;
+  __shared__ int order[64];
+  const int lane = __lane_id();
   const int64_t base = (int64_t)blockIdx.x * per_block;
   const int count = n - base < per_block ? (int)(n - base) : per_block;
-  spotfit_shape_t sh{0, 0, 0, 0};
-  int64_t off = 0;
-  if (lane < count) {
-    sh = sizes[base + lane];
-    off = offsets[base + lane];
-  }
-  const bool ok = lane < count && usable<L>(sh, max_side, max_pixels);
-  const uint64_t m_ok = __builtin_amdgcn_ballot_w64(ok);
-  if (m_ok != 0) {
-    const int some = (int)__builtin_ctzll(m_ok);
-    const int2 o2 = __builtin_bit_cast(int2, off);
-    const int whs = sh.w | sh.h << 8;
-#pragma unroll 1
-    for (int i = 0; i < count; i += G) {
-      const int want = i + g < count ? i + g : count - 1;
-      const int from = (m_ok >> want & 1) ? want : some;
-      const int wh = pick(whs, from);
-      const int w = wh & 0xff, h = wh >> 8;
-      const int64_t o = __builtin_bit_cast(int64_t, make_int2(pick(o2.x, from), pick(o2.y, from)));
-      Row<L> row;
-      load_row<L>(data + o, w, h, r, row);
-      // 36 / (rows x columns of the window), for inner and for edge columns
-      const bool row_edge = r == 0 || r == h - 1;
-      const uint32_t inner = r < h ? (row_edge ? 6u * 32 : 4u * 32) : 0u;
-      const uint32_t edge = r < h ? (row_edge ? 9u * 32 : 6u * 32) : 0u;
-      uint32_t best = 0, left = 0, mid = row.v[0] & 0xffffu;
-      uint32_t hi2 = 0, lo2 = 0xffffffffu;
-#pragma unroll
-      for (int c = 0; c < L; ++c) {
-        const uint32_t right = c + 1 < L ? (c & 1 ? row.v[(c + 1) / 2 < L / 2 ? (c + 1) / 2 : 0] & 0xffffu
-                                                  : row.v[c / 2] >> 16)
-                                         : 0u;
-        const uint32_t across = left + mid + right;
-        uint32_t up, down;
-        if constexpr (L == 16) {  // a group is a DPP row: zeros come in at its ends
-          up = (uint32_t)dpp_i<0x111>((int)across);    // row_shr:1
-          down = (uint32_t)dpp_i<0x101>((int)across);  // row_shl:1
-        } else {
-          up = (uint32_t)dpp_i<0x138>((int)across);    // wave_shr:1
-          down = (uint32_t)dpp_i<0x130>((int)across);  // wave_shl:1
-          up = r == 0 ? 0u : up;
-          down = r == L - 1 ? 0u : down;
-        }
-        const uint32_t mult = c == 0 ? edge : c < w - 1 ? inner : c == w - 1 ? edge : 0u;
-        const uint32_t key = (across + up + down) * mult + uint32_t(31 - c);
-        best = key > best ? key : best;
-        left = mid;
-        mid = right;
-      }
-      // smallest and largest pixel of the row
-#pragma unroll
-      for (int p = 0; p < L / 2; ++p) {
-        hi2 = max2(hi2, row.v[p]);
-        const uint32_t past = 2 * p >= w ? 0xffffffffu : 2 * p + 1 >= w ? 0xffff0000u : 0u;
-        lo2 = min2(lo2, row.v[p] | past);
-      }
-      uint32_t hi = (hi2 & 0xffffu) > hi2 >> 16 ? hi2 & 0xffffu : hi2 >> 16;
-      uint32_t lo = (lo2 & 0xffffu) < lo2 >> 16 ? lo2 & 0xffffu : lo2 >> 16;
-      lo = r < h ? lo : 0xffffu;
-      hi = gmax_u<L>(hi);
-      lo = gmin_u<L>(lo);
-      // the group's brightest window: the first row among the largest means
-      const uint32_t mean = best >> 5, top = gmax_u<L>(mean);
-      const uint32_t at = gmin_u<L>(mean == top && r < h ? uint32_t(r) << 5 | (31u - (best & 31u)) : 0xffffffffu);
-      const double thr = __builtin_fma(double(hi) - double(lo), kExpMinusHalf, double(lo));
-      // g > thr is g > floor(thr): count max(g - floor(thr), 0) != 0
-      const uint32_t f = (uint32_t)thr, f2 = f | f << 16;
-      uint32_t m = 0;
-#pragma unroll
-      for (int p = 0; p < L / 2; ++p) m = dot2(min2(sub_sat(row.v[p], f2), 0x10001u), 0x10001u, m);
-      m = (uint32_t)gsum_i<L>((int)m);
-      if (r == 0 && i + g < count) {
-        where[i + g] = at;
-        area[i + g] = m;
-      }
-    }
-  }
+  const Batch b = take_batch<LMAX>(sizes, offsets, base, count, max_side, max_pixels, order);
+  const bool ok = b.ok;
+  peak_rows<8>(b, data, order, where, area);
+  if constexpr (LMAX >= 16) peak_rows<16>(b, data, order, where, area);
+  if constexpr (LMAX >= 32) peak_rows<32>(b, data, order, where, area);
   __syncthreads();
   if (lane < count) {
     const float nanf = __builtin_nanf("");
