@@ -363,8 +363,15 @@ __device__ __forceinline__ void put_totals(const Lane& ln, Shared<NS>& L, int sl
 }
 
 // Residuals r = alpha f + beta - g of row tile AT, window Q (B columns): their
-// squares added to cs, one sum per column of the lane.  aex: alpha ex.
-template <int AT, int B, int DT>
+// squares added to cs, one sum per column of the lane.  aex: alpha ex.  KIND: how
+// rows below the spot are left out (1M floats of 15x15 1.26 ms with selects
+// everywhere, 1.21 so; 36,600 of 32x32 251 us, 239).
+enum class Rows {
+  kAll,     // there are none in this tile
+  kBranch,  // by a branch
+  kSelect,  // by a select of each sum, two instructions a pixel
+};
+template <int AT, int B, Rows KIND, int DT>
 __device__ __forceinline__ void residual_row(const Lane& ln, const Raw<DT>& px, const double (&aex)[4],
                                              double eyq, double beta, int h, double (&cs)[4]) {
   // row 4 AT + v is with lane AT % 4 of the quad of row group v
@@ -374,11 +381,18 @@ __device__ __forceinline__ void residual_row(const Lane& ln, const Raw<DT>& px, 
                             __builtin_amdgcn_ds_bpermute(src << 2, u.y));
   const double e = __builtin_bit_cast(double, r2);
   const bool rowin = 4 * AT + ln.v < h;
-  unrolled<B>([&](auto bi) {
-    constexpr int t = decltype(bi)::value;
-    const double res = __builtin_fma(aex[t], e, beta - px.template get<t>());
-    cs[t] = rowin ? __builtin_fma(res, res, cs[t]) : cs[t];
-  });
+  auto add = [&] {
+    unrolled<B>([&](auto bi) {
+      constexpr int t = decltype(bi)::value;
+      const double res = __builtin_fma(aex[t], e, beta - px.template get<t>());
+      cs[t] = KIND != Rows::kSelect || rowin ? __builtin_fma(res, res, cs[t]) : cs[t];
+    });
+  };
+  if constexpr (KIND == Rows::kBranch) {
+    if (rowin) add();
+  } else {
+    add();
+  }
 }
 
 // Sums of g and g^2 over a spot's own pixels, from its lanes' partial sums.
@@ -561,10 +575,11 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
       });
       unrolled<TB>([&](auto ai) {
         constexpr int at = decltype(ai)::value, i = kRing ? TB + at : at;
+        constexpr Rows kRowsOut = at == TB - 1 || TB == 2 ? Rows::kBranch : Rows::kAll;
         if constexpr (kRing) put_back(ai, px[i % kRows]);
         unrolled<CH>([&](auto qi) {
           constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
-          residual_row<at, B>(ln, px[i % kRows][q].fresh(), aex[q], eyq[at / 4], am.b, win.h, cs[q]);
+          residual_row<at, B, kRowsOut>(ln, px[i % kRows][q].fresh(), aex[q], eyq[at / 4], am.b, win.h, cs[q]);
         });
         if constexpr (kRing) refill(std::integral_constant<int, i>{});
         else load_next(px[at]);
@@ -624,7 +639,7 @@ __device__ __forceinline__ void sum_residuals(const void* data, Shared<NS>& L, i
           constexpr int at = decltype(ai)::value;
           if (at < Hm) {
             px[at].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
-            residual_row<at, 4>(ln, px[at], aex, eyq[at / 4], beta, win.h, cs);
+            residual_row<at, 4, Rows::kBranch>(ln, px[at], aex, eyq[at / 4], beta, win.h, cs);
           }
         });
         unrolled<4>([&](auto bi) {
@@ -782,9 +797,13 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
         cs[q][t] = 0.0;
       });
     };
+    // of 4 wide slots the row tiles stay one run of code: a lone wavefront waits
+    // for its own instructions (32 spots of 17x17 23.6 us so, 24.1 with branches)
+    constexpr Rows kRowsOut = NS == 4 && CQ > 1 ? Rows::kSelect : Rows::kBranch;
     auto window = [&](auto ai, auto qi, const Raw<DT>& g) {
       constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
-      residual_row<decltype(ai)::value, B>(ln, g.fresh(), aex[q], eyq[decltype(ai)::value / 4], am.b, win.h, cs[q]);
+      residual_row<decltype(ai)::value, B, kRowsOut>(ln, g.fresh(), aex[q], eyq[decltype(ai)::value / 4], am.b,
+                                                     win.h, cs[q]);
     };
     auto add_up = [&](auto qi) {
       constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
@@ -859,7 +878,7 @@ __device__ __forceinline__ double block_residuals_of(const Lane& ln, const Raw<D
     });
     unrolled<TB>([&](auto ai) {
       constexpr int at = decltype(ai)::value;
-      residual_row<at, B>(ln, px[at][q].fresh(), aex, eyq[at / 4], beta, win.h, cs);
+      residual_row<at, B, Rows::kBranch>(ln, px[at][q].fresh(), aex, eyq[at / 4], beta, win.h, cs);
     });
     unrolled<B>([&](auto bi) {
       constexpr int t = decltype(bi)::value;
