@@ -350,6 +350,23 @@ __device__ __forceinline__ void factors(const Lane& ln, const Window<CH, DT>& wi
   ex = ln.v < win.own[Q] ? fac[0] : 0.0;
   ey = row < win.h ? fac[1] : 0.0;
 }
+// One of the two, where a spot has more windows of columns than quads of row
+// tiles or the other way round.
+template <int Q, int CH, int DT>
+__device__ __forceinline__ double column_factor(const Lane& ln, const Window<CH, DT>& win, double x, double hx) {
+  const double dxc = double(win.start[Q] + ln.v) - x;
+  double arg[1] = {dxc * dxc * hx}, fac[1];
+  exp_neg_n<1>(arg, fac);
+  return ln.v < win.own[Q] ? fac[0] : 0.0;
+}
+template <int Q, int CH, int DT>
+__device__ __forceinline__ double row_factor(const Lane& ln, const Window<CH, DT>& win, double y, double hy) {
+  const int row = 16 * Q + 4 * ln.v + ln.k;
+  const double dyr = double(row) - y;
+  double arg[1] = {dyr * dyr * hy}, fac[1];
+  exp_neg_n<1>(arg, fac);
+  return row < win.h ? fac[0] : 0.0;
+}
 
 // The entry of R, GX and GY that this lane holds, to the slot's totals.
 template <int NS>
@@ -415,7 +432,11 @@ __device__ __forceinline__ Amplitudes slot_amplitudes(const Shared<NS>& L, int s
 
 // Evaluates the cnt > 0 slots of L.order, the first cnt_new of them new spots,
 // at their candidates, four a pass (Eqs. 2, 5-7, 10), into L.tot.  Every slot
-// has the shape of geo0, with TB columns per lane group and TB row tiles.  Float
+// has the shape of geo0, with TB columns per lane group and TR row tiles or, if
+// RECT, at most TR row tiles: those below the spots are branched over (uneven
+// spots of one shape in the passes for mixed shapes, over the tiles of their
+// larger side both ways, / so: 1M of 16-bit 8x32 2.71 ms / 1.21, 16x6 1.21 / 0.82;
+// of float 32x8 4.41 / 2.02, 16x6 1.67 / 1.26; lane-owned 3.61, 1.00, 3.50, 1.01).  Float
 // data: with chi^2 summed over the pixels.
 //
 // The pixels of a pass stay in registers, and the next pass's take their places
@@ -423,12 +444,12 @@ __device__ __forceinline__ Amplitudes slot_amplitudes(const Shared<NS>& L, int s
 // the owners' state out of the registers, kRows row tiles are in flight instead,
 // read once for the products and once for the residuals (200,000 of 17x17:
 // 826 us held, 683 read twice).
-template <int NS, int DT, int TB>
+template <int NS, int DT, int TB, int TR, bool RECT>
 __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L, int cnt, int cnt_new,
                                                  uint32_t geo0) {
-  constexpr int CH = (TB + 3) / 4;
-  constexpr bool kFloat = DT != SPOTFIT_U16, kRing = kFloat && CH > 1;
-  constexpr int kRows = kRing ? 4 : TB;
+  constexpr int CH = (TB + 3) / 4, CR = (TR + 3) / 4;  // windows of columns, quads of row tiles
+  constexpr bool kFloat = DT != SPOTFIT_U16, kRing = kFloat && (CH > 1 || CR > 1);
+  constexpr int kRows = kRing ? 4 : TR;
   // opaque: a lane's constants are formed once a step here, not held in
   // registers over the rest of it
   int lane = __lane_id();
@@ -436,6 +457,8 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   const Lane ln(lane);
   Window<CH, DT> win;
   win.set(geo0, ln.v, ln.k);
+  const int rows = int((geo0 >> 8 & 0xffu) + 3) >> 2;  // row tiles of the spots
+  auto in = [&](int at) { return !RECT || at < rows; };
   Raw<DT> px[kRows][CH];
   auto slot_at = [&](int p) { return L.order[p + ln.blk < cnt ? p + ln.blk : cnt - 1]; };
   const char* base[CH];
@@ -458,23 +481,34 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   // come back
   auto put_back = [&](auto ai, Raw<DT> (&row)[CH]) {
     constexpr int at = decltype(ai)::value;
-    if constexpr (at == TB - 1 || TB == 2) {
+    if constexpr (RECT || at == TR - 1 || TR == 2) {
+      if (RECT && at != rows - 1) return;
 #pragma unroll
       for (int q = 0; q < CH; ++q) row[q].shift(4 * at + ln.v >= win.h - 1 ? win.over[q] : 0);
     }
   };
-  // after item i of a ring pass (TB row tiles for the products, then for the
+  // after item i of a ring pass (TR row tiles for the products, then for the
   // residuals): the item that takes its place
   auto refill = [&](auto ii) {
     constexpr int i = decltype(ii)::value + kRows;
-    if constexpr (i < 2 * TB) {
-      if constexpr (i == TB) rewind();
+    if constexpr (i < 2 * TR) {
+      if constexpr (i == TR) rewind();
       load_next(px[i % kRows]);
     }
   };
+  // RECT: row tile a is in place a % kRows both times; after the products (then
+  // the residuals) of tile at, the next tile of that place, or the first one again
+  auto refill_rect = [&](auto ai, bool again) {
+    constexpr int at = decltype(ai)::value;
+    const bool more = at + kRows < rows;
+    if (!more && !again) return;
+    rb = win.row + (more ? uint32_t(at + kRows) : uint32_t(at % kRows)) * win.step;
+    asm volatile("" : "+v"(rb));
+    load_next(px[at % kRows]);
+  };
   auto add_row = [&](auto ai, const Raw<DT> (&row)[CH], double& sg, double& sgg) {
     constexpr int at = decltype(ai)::value;
-    const bool rowin = (at < TB - 1 && TB > 2) || 4 * at + ln.v < win.h;
+    const bool rowin = (!RECT && at < TR - 1 && TR > 2) || 4 * at + ln.v < win.h;
     unrolled<TB>([&](auto bi) {
       constexpr int t = decltype(bi)::value;
       const double g = row[t / 4].template get<t % 4>();
@@ -489,7 +523,9 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   if constexpr (!kRing) {
     aim(slot);
     rb = win.row;
-    unrolled<TB>([&](auto ai) { load_next(px[decltype(ai)::value]); });
+    unrolled<TR>([&](auto ai) {
+      if (in(decltype(ai)::value)) load_next(px[decltype(ai)::value]);
+    });
   }
 
 #pragma unroll 1
@@ -501,7 +537,8 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
       if (p < cnt_new) {
         double sg = 0.0, sgg = 0.0;
         rewind();
-        unrolled<TB>([&](auto ai) {
+        unrolled<TR>([&](auto ai) {
+          if (!in(decltype(ai)::value)) return;
           Raw<DT> row[CH];
           load_next(row);
           put_back(ai, row);
@@ -510,7 +547,9 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
         put_pixel_sums(ln, L, cslot, p + ln.blk < cnt_new, sg, sgg);
       }
       rewind();
-      unrolled<kRows>([&](auto ai) { load_next(px[decltype(ai)::value]); });
+      unrolled<kRows>([&](auto ai) {
+        if (in(decltype(ai)::value)) load_next(px[decltype(ai)::value]);
+      });
     }
     // the next pass (or this one's last slot again): its rows are loaded as this
     // pass's are used
@@ -519,29 +558,38 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
       aim(slot);
       rewind();
     }
-    double exq[CH], eyq[CH], V[TB], E[TB];
+    double exq[CH], eyq[CR], V[TB], E[TR];
     double R = 0.0, GX = 0.0, GY = 0.0;
-    unrolled<CH>([&](auto qi) {
+    unrolled<(CH > CR ? CH : CR)>([&](auto qi) {
       constexpr int q = decltype(qi)::value;
-      factors<q>(ln, win, x, y, hx, hy, exq[q], eyq[q]);
+      if constexpr (q < CH && q < CR) {
+        factors<q>(ln, win, x, y, hx, hy, exq[q], eyq[q]);
+      } else if constexpr (q < CH) {
+        exq[q] = column_factor<q>(ln, win, x, hx);
+      } else {
+        eyq[q] = rows > 4 * q ? row_factor<q>(ln, win, y, hy) : 0.0;
+      }
     });
     const double dy0 = double(ln.k) - y;
-    unrolled<TB>([&](auto ti) {
+    unrolled<(TB > TR ? TB : TR)>([&](auto ti) {
       constexpr int t = decltype(ti)::value;
-      const double dx = (double(win.start[t / 4]) - x) + double(t % 4);
-      V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
-      E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
-      GX = mfma4(V[t], V[t], GX);
-      GY = mfma4(E[t], E[t], GY);
+      if constexpr (t < TB) {
+        const double dx = (double(win.start[t / 4]) - x) + double(t % 4);
+        V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
+      }
+      if constexpr (t < TR) E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
+      if constexpr (t < TB) GX = mfma4(V[t], V[t], GX);
+      if constexpr (t < TR) GY = mfma4(E[t], E[t], GY);
       if constexpr (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (!kRing) {
-      unrolled<TB>([&](auto ai) { put_back(ai, px[decltype(ai)::value]); });
+      unrolled<TR>([&](auto ai) { put_back(ai, px[decltype(ai)::value]); });
       if (p < cnt_new) {
         double sg = 0.0, sgg = 0.0;
-        unrolled<TB>([&](auto ai) {
+        unrolled<TR>([&](auto ai) {
           constexpr int at = decltype(ai)::value;
+          if (!in(at)) return;
           Raw<DT> row[CH];
 #pragma unroll
           for (int q = 0; q < CH; ++q) row[q] = px[at][q].fresh();
@@ -550,8 +598,9 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
         put_pixel_sums(ln, L, cslot, p + ln.blk < cnt_new, sg, sgg);
       }
     }
-    unrolled<TB>([&](auto ai) {
+    unrolled<TR>([&](auto ai) {
       constexpr int at = decltype(ai)::value;
+      if (!in(at)) return;
       if constexpr (kRing) put_back(ai, px[at % kRows]);
       double S = 0.0;
       unrolled<TB>([&](auto bi) {
@@ -559,7 +608,8 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
         S = mfma4(px[at % kRows][t / 4].template get<t % 4>(), V[t], S);
       });
       R = mfma4(E[at], S, R);
-      if constexpr (kRing) refill(ai);
+      if constexpr (kRing && RECT) refill_rect(ai, true);
+      else if constexpr (kRing) refill(ai);
       else if constexpr (!kFloat) load_next(px[at]);
       __builtin_amdgcn_sched_barrier(0);  // bounds the tiles in flight (registers)
     });
@@ -573,15 +623,17 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
         aex[t / 4][t % 4] = am.a * lg::gbcast<4, t % 4>(exq[t / 4]);
         cs[t / 4][t % 4] = 0.0;
       });
-      unrolled<TB>([&](auto ai) {
-        constexpr int at = decltype(ai)::value, i = kRing ? TB + at : at;
-        constexpr Rows kRowsOut = at == TB - 1 || TB == 2 ? Rows::kBranch : Rows::kAll;
+      unrolled<TR>([&](auto ai) {
+        constexpr int at = decltype(ai)::value, i = kRing && !RECT ? TR + at : at;
+        constexpr Rows kRowsOut = RECT || at == TR - 1 || TR == 2 ? Rows::kBranch : Rows::kAll;
+        if (!in(at)) return;
         if constexpr (kRing) put_back(ai, px[i % kRows]);
         unrolled<CH>([&](auto qi) {
           constexpr int q = decltype(qi)::value, B = TB - 4 * q < 4 ? TB - 4 * q : 4;
           residual_row<at, B, kRowsOut>(ln, px[i % kRows][q].fresh(), aex[q], eyq[at / 4], am.b, win.h, cs[q]);
         });
-        if constexpr (kRing) refill(std::integral_constant<int, i>{});
+        if constexpr (kRing && RECT) refill_rect(ai, false);
+        else if constexpr (kRing) refill(std::integral_constant<int, i>{});
         else load_next(px[at]);
         __builtin_amdgcn_sched_barrier(0);
       });
@@ -1179,9 +1231,11 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         w = geo & 0xff;
         h = (geo >> 8) & 0xff;
         const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0) & 0xffffu;
-        const int T = ((geo0 & 0xff) + 3) >> 2;
-        const bool uni = T == (int)((geo0 >> 8) + 3) >> 2 &&
-                         __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
+        const int T = ((geo0 & 0xff) + 3) >> 2, Tr = ((geo0 >> 8) + 3) >> 2;
+        // (16 slots, which batches of 8,000 to 32,000 spots take, have no passes for
+        // uneven sides: their code made every step 2 % longer)
+        constexpr bool kMany = NS > 16;
+        const bool uni = (kMany || T == Tr) && __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
         int rank = 0;
         if (uni) {  // new spots first, so that few passes form their sums of g and g^2
           rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
@@ -1201,7 +1255,11 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
           const int cnt_new = __builtin_popcountll(m_new);
           unrolled<4 * CH - 1>([&](auto ti) {
             constexpr int TB = decltype(ti)::value + 2;
-            if (T == TB || (TB == 2 && T < 2)) evaluate_uniform<NS, DT, TB>(data, L, cnt, cnt_new, geo0);
+            if (T != TB && !(TB == 2 && T < 2)) return;
+            if (!kMany || Tr == TB || (TB == 2 && Tr < 2))
+              evaluate_uniform<NS, DT, TB, TB, false>(data, L, cnt, cnt_new, geo0);
+            else if constexpr (kMany)
+              evaluate_uniform<NS, DT, TB, 4 * CH, true>(data, L, cnt, cnt_new, geo0);
           });
         } else {
           evaluate_any<NS, CH, DT>(data, L, cnt);
