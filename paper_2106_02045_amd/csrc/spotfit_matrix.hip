@@ -437,14 +437,15 @@ __device__ __forceinline__ Amplitudes slot_amplitudes(const Shared<NS>& L, int s
 // spots of one shape in the passes for mixed shapes, over the tiles of their
 // larger side both ways, / so: 1M of 16-bit 8x32 2.71 ms / 1.21, 16x6 1.21 / 0.82;
 // of float 32x8 4.41 / 2.02, 16x6 1.67 / 1.26; lane-owned 3.61, 1.00, 3.50, 1.01).  Float
-// data: with chi^2 summed over the pixels.
+// data: with chi^2 summed over the pixels.  ANY (two tiles each way): slots of any
+// shapes up to 8 x 8.
 //
 // The pixels of a pass stay in registers, and the next pass's take their places
 // as they are used; of floats above 16 px, whose 40 to 64 registers would push
 // the owners' state out of the registers, kRows row tiles are in flight instead,
 // read once for the products and once for the residuals (200,000 of 17x17:
 // 826 us held, 683 read twice).
-template <int NS, int DT, int TB, int TR, bool RECT>
+template <int NS, int DT, int TB, int TR, bool RECT, bool ANY = false>
 __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L, int cnt, int cnt_new,
                                                  uint32_t geo0) {
   constexpr int CH = (TB + 3) / 4, CR = (TR + 3) / 4;  // windows of columns, quads of row tiles
@@ -455,27 +456,30 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   int lane = __lane_id();
   asm volatile("" : "+v"(lane));
   const Lane ln(lane);
-  Window<CH, DT> win;
-  win.set(geo0, ln.v, ln.k);
+  static_assert(!ANY || (TB == 2 && TR == 2), "every row and column is checked");
+  Window<CH, DT> win, win_next;
+  if constexpr (!ANY) win.set(geo0, ln.v, ln.k);
+  Window<CH, DT>& ahead = ANY ? win_next : win;  // of the pixels to load
   const int rows = int((geo0 >> 8 & 0xffu) + 3) >> 2;  // row tiles of the spots
   auto in = [&](int at) { return !RECT || at < rows; };
   Raw<DT> px[kRows][CH];
   auto slot_at = [&](int p) { return L.order[p + ln.blk < cnt ? p + ln.blk : cnt - 1]; };
   const char* base[CH];
   auto aim = [&](int sl) {  // at the first rows of a slot's windows
+    if constexpr (ANY) ahead.set(L.geo[sl], ln.v, ln.k);
     const char* p = static_cast<const char*>(data) + L.off[sl] * Raw<DT>::kSize;
 #pragma unroll
-    for (int q = 0; q < CH; ++q) base[q] = p + win.start[q] * Raw<DT>::kSize;
+    for (int q = 0; q < CH; ++q) base[q] = p + ahead.start[q] * Raw<DT>::kSize;
   };
   uint32_t rb;
   auto rewind = [&] {
-    rb = win.row;
+    rb = ahead.row;
     if constexpr (CH > 1) asm volatile("" : "+v"(rb));  // its rows' offsets do not fit the registers
   };
   auto load_next = [&](Raw<DT> (&to)[CH]) {
 #pragma unroll
-    for (int q = 0; q < CH; ++q) to[q].load(base[q] + (rb < win.last[q] ? rb : win.last[q]));
-    rb += win.step;
+    for (int q = 0; q < CH; ++q) to[q].load(base[q] + (rb < ahead.last[q] ? rb : ahead.last[q]));
+    rb += ahead.step;
   };
   // the last row tile holds the last row (of two: either): windows cut off there
   // come back
@@ -522,7 +526,7 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   int slot = slot_at(0);
   if constexpr (!kRing) {
     aim(slot);
-    rb = win.row;
+    rb = ahead.row;
     unrolled<TR>([&](auto ai) {
       if (in(decltype(ai)::value)) load_next(px[decltype(ai)::value]);
     });
@@ -532,6 +536,7 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
   for (int p = 0; p < cnt; p += 4) {
     const double x = L.x[slot], y = L.y[slot], hx = L.hx[slot], hy = L.hy[slot];
     const int cslot = slot;
+    if constexpr (ANY) win = win_next;
     if constexpr (kRing) {
       aim(slot);
       if (p < cnt_new) {
@@ -1232,12 +1237,16 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         h = (geo >> 8) & 0xff;
         const uint32_t geo0 = (uint32_t)__builtin_amdgcn_readlane((int)geo, lead0) & 0xffffu;
         const int T = ((geo0 & 0xff) + 3) >> 2, Tr = ((geo0 >> 8) + 3) >> 2;
-        // (16 slots, which batches of 8,000 to 32,000 spots take, have no passes for
-        // uneven sides: their code made every step 2 % longer)
+        // (16 slots, which batches of 8,000 to 32,000 spots take, have neither of the
+        // two kinds of passes below: their code made every step 2 % longer)
         constexpr bool kMany = NS > 16;
         const bool uni = (kMany || T == Tr) && __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
+        // small spots of any shapes go through passes of two tiles, the next one's
+        // pixels ahead: 1M of 4..8 px 810 us of 16-bit pixels (910 in passes by size),
+        // 1015 of floats (1150)
+        const bool small = kMany && !uni && __builtin_amdgcn_ballot_w64(act && tiles_of(geo) > 2) == 0;
         int rank = 0;
-        if (uni) {  // new spots first, so that few passes form their sums of g and g^2
+        if (uni || small) {  // new spots first, so that few passes form their sums of g and g^2
           rank = fresh ? rank_of(m_new) : rank_of(m_act & ~m_new) + __builtin_popcountll(m_new);
         } else {  // by size, so that few passes go over the tiles of a large spot
           const int tiles = tiles_of(geo);
@@ -1251,8 +1260,10 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         }
         if (act) L.order[rank] = own;
         wave_lds_sync();
-        if (uni) {
-          const int cnt_new = __builtin_popcountll(m_new);
+        const int cnt_new = __builtin_popcountll(m_new);
+        if (small) {
+          if constexpr (kMany) evaluate_uniform<NS, DT, 2, 2, false, true>(data, L, cnt, cnt_new, geo0);
+        } else if (uni) {
           unrolled<4 * CH - 1>([&](auto ti) {
             constexpr int TB = decltype(ti)::value + 2;
             if (T != TB && !(TB == 2 && T < 2)) return;

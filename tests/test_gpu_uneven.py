@@ -28,3 +28,13 @@ def test_one_uneven_shape(slots, f32):
             b.init[:, 2:] *= 2.0
         for side in {max(w, h), 32}:
             _equal(_fit(b, slots, max_side=side), _fit(b, 16, max_side=side, schedule=1))
+
+
+@pytest.mark.parametrize("f32", [False, True])
+@pytest.mark.parametrize("slots", [32, 64])
+def test_small_spots_of_any_shapes(slots, f32):
+    shapes = [(w, h) for w in range(3, 9) for h in range(3, 9)]
+    _, b, _ = _shapes(shapes, 11, f32)
+    ref = _fit(b, 16)
+    _equal(_fit(b, slots, max_side=8), ref)
+    _equal(_fit(b, slots, schedule=1), ref)
