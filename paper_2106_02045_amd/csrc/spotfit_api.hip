@@ -578,7 +578,8 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
       kc.status_out = status_out + c0;
       kc.evals_out = evals_out ? evals_out + 2 * c0 : nullptr;
       e = sf::launch_matrix_kernel(kMatrixSlots[si], wide, kc, lists ? &ws : nullptr, resident,
-                                   mixed ? ctx->n_cu : 0, (hipStream_t)stream);
+                                   mixed ? ctx->n_cu : 0,
+                                   kc.n <= 4 * kMatrixSlots[0] * (int64_t)ctx->n_cu, (hipStream_t)stream);
     }
   } else if (o.precision == SPOTFIT_PREC_FP64 && o.schedule == SPOTFIT_SCHEDULE_MIXED) {
     if (!classified && !own_ws && n > ctx->ws_cap) {

@@ -139,14 +139,15 @@ hipError_t launch_narrow_mixed_fit(int plan, const KArgs& ka, const MixedWs& ws,
 // `slots` spots per wavefront: 4, 16, 32 or 64, the same bits for each.  `resident`:
 // wavefronts to launch at most; a batch of more spots than they hold draws the
 // rest from kMatrixCounters counters, one cache line each, at ka.queue (cleared
-// here).  spread: a batch for 4 slots goes to this many wavefronts first.  ws:
+// here).  spread: a batch for 4 slots goes to this many wavefronts first.  lone: no more
+// wavefronts than SIMDs.  ws:
 // class lists to go through, largest class first, or null: spots in order.  ka.n
 // <= 2^30; reads ka.init.
 constexpr int kMatrixCounters = 32;
 constexpr int kMatrixCounterWords = 32;  // from one counter to the next
 const void* matrix_kernel_symbol(int slots, bool wide, int dtype);
 hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const MixedWs* ws, int resident,
-                                int spread, hipStream_t st);
+                                int spread, bool lone, hipStream_t st);
 // The classify pass of a mixed-size launch alone.
 hipError_t launch_classify(const KArgs& ka, const MixedWs& ws, hipStream_t st);
 

@@ -729,7 +729,7 @@ struct Candidate {
 // One pass over four slots of any shapes (this lane's block has `slot`, of shape
 // geo) at their candidates, into L.tot.  load: read their pixels first, at `off`,
 // into px, shifted into place; else px holds them.  sums: some slot (fresh) is a
-// new spot.  Every slot has at most TB columns per lane group and TB row tiles;
+// new spot.  Every slot has at most TB columns per lane group and TR row tiles;
 // the tiles that a smaller one does not have add zeros to its sums, so it has
 // the same bits in every company.
 //
@@ -739,13 +739,13 @@ struct Candidate {
 // pixels read at each step), 1,024 of 11x11 18.0 (19.5), 4,000 raw spots of
 // 9..21 px 41.0 (47.3).  Of more slots, wide floats go through a ring of row tiles as
 // in evaluate_uniform.
-template <int NS, int CH, int DT, int TB>
+template <int NS, int CH, int DT, int TB, int TR>
 __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, Shared<NS>& L, int slot,
                                               Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
                                               uint32_t geo, bool load, bool sums, bool fresh) {
-  constexpr int CQ = (TB + 3) / 4;
+  constexpr int CQ = (TB + 3) / 4, CR = (TR + 3) / 4;
   constexpr bool kFloat = DT != SPOTFIT_U16, kRing = NS > 4 && kFloat && CQ > 1;
-  constexpr int kRows = kRing ? 4 : TB;
+  constexpr int kRows = kRing ? 4 : TR;
   Window<CQ, DT> win;
   win.set(geo, ln.v, ln.k);
   const char* base = static_cast<const char*>(data) + off * Raw<DT>::kSize;
@@ -764,8 +764,8 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
   };
   auto refill = [&](auto ii) {  // after item i of the ring
     constexpr int i = decltype(ii)::value + kRows;
-    if constexpr (i < 2 * TB) {
-      if constexpr (i == TB) rb = win.row;
+    if constexpr (i < 2 * TR) {
+      if constexpr (i == TR) rb = win.row;
       load_next(px[i % kRows]);
     }
   };
@@ -786,7 +786,7 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
   if constexpr (kRing) {
     if (sums) {
       double sg = 0.0, sgg = 0.0;
-      unrolled<TB>([&](auto ai) {
+      unrolled<TR>([&](auto ai) {
         Raw<DT> row[CH];
         load_next(row);
         put_back(ai, row);
@@ -797,26 +797,35 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
     }
   }
   if (load) unrolled<kRows>([&](auto ai) { load_next(px[decltype(ai)::value]); });
-  double exq[CQ], eyq[CQ], V[TB], E[TB];
+  double exq[CQ], eyq[CR], V[TB], E[TR];
   double R = 0.0, GX = 0.0, GY = 0.0;
-  unrolled<CQ>([&](auto qi) {
+  unrolled<(CQ > CR ? CQ : CR)>([&](auto qi) {
     constexpr int q = decltype(qi)::value;
-    factors<q>(ln, win, c.x, c.y, c.hx, c.hy, exq[q], eyq[q]);
+    if constexpr (q < CQ && q < CR)
+      factors<q>(ln, win, c.x, c.y, c.hx, c.hy, exq[q], eyq[q]);
+    else if constexpr (q < CQ)
+      exq[q] = column_factor<q>(ln, win, c.x, c.hx);
+    else
+      eyq[q] = row_factor<q>(ln, win, c.y, c.hy);
   });
   const double dy0 = double(ln.k) - c.y;
-  unrolled<TB>([&](auto ti) {
+  unrolled<(TB > TR ? TB : TR)>([&](auto ti) {
     constexpr int t = decltype(ti)::value;
-    const double dx = (double(win.start[t / 4]) - c.x) + double(t % 4);
-    V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
-    GX = mfma4(V[t], V[t], GX);
-    E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
-    GY = mfma4(E[t], E[t], GY);
+    if constexpr (t < TB) {
+      const double dx = (double(win.start[t / 4]) - c.x) + double(t % 4);
+      V[t] = vector_entry(ln, lg::gbcast<4, t % 4>(exq[t / 4]), dx);
+      GX = mfma4(V[t], V[t], GX);
+    }
+    if constexpr (t < TR) {
+      E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
+      GY = mfma4(E[t], E[t], GY);
+    }
   });
   if constexpr (!kRing) {
-    if (load) put_back_from<TB - 1>(px, last_tile, put_back);
+    if (load) put_back_from<TR - 1>(px, last_tile, put_back);
     if (sums) {
       double sg = 0.0, sgg = 0.0;
-      unrolled<TB>([&](auto ai) {
+      unrolled<TR>([&](auto ai) {
         constexpr int at = decltype(ai)::value;
         Raw<DT> row[CH];
 #pragma unroll
@@ -826,7 +835,7 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
       put_pixel_sums(ln, L, slot, fresh, sg, sgg);
     }
   }
-  unrolled<TB>([&](auto ai) {
+  unrolled<TR>([&](auto ai) {
     constexpr int at = decltype(ai)::value;
     if constexpr (kRing) put_back(ai, px[at % kRows]);
     Raw<DT> row[CQ];
@@ -871,8 +880,8 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
     };
     if constexpr (kRing) {  // row by row, as the ring goes
       unrolled<CQ>(scale);
-      unrolled<TB>([&](auto ai) {
-        constexpr int i = TB + decltype(ai)::value;
+      unrolled<TR>([&](auto ai) {
+        constexpr int i = TR + decltype(ai)::value;
         put_back(ai, px[i % kRows]);
         unrolled<CQ>([&](auto qi) { window(ai, qi, px[i % kRows][decltype(qi)::value]); });
         refill(std::integral_constant<int, i>{});
@@ -882,7 +891,7 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
     } else {  // window by window: fewer registers
       unrolled<CQ>([&](auto qi) {
         scale(qi);
-        unrolled<TB>([&](auto ai) {
+        unrolled<TR>([&](auto ai) {
           window(ai, qi, px[decltype(ai)::value][decltype(qi)::value]);
           __builtin_amdgcn_sched_barrier(0);
         });
@@ -894,16 +903,25 @@ __device__ __forceinline__ void evaluate_pass(const void* data, const Lane& ln, 
   }
 }
 
-// The pass with the tiles of the largest of its four slots.
-template <int NS, int CH, int DT>
+// The pass with the tiles of the largest of its four slots.  UNEVEN: with four row
+// tiles, or four columns per lane group, where no spot has more and more the other way.
+template <int NS, int CH, int DT, bool UNEVEN>
 __device__ __forceinline__ void evaluate_four(const void* data, const Lane& ln, Shared<NS>& L, int slot,
                                               Raw<DT> (&px)[4 * CH][CH], const Candidate& c, int64_t off,
                                               uint32_t geo, bool load, bool sums, bool fresh) {
   const int tiles = max_over_blocks(tiles_of(geo));
+  const int cols = UNEVEN ? max_over_blocks((int(geo & 0xff) + 3) >> 2) : tiles;
+  const int rows = UNEVEN ? max_over_blocks((int(geo >> 8 & 0xff) + 3) >> 2) : tiles;
   unrolled<4 * CH - 1>([&](auto ti) {
     constexpr int TB = decltype(ti)::value + 2;
-    if (tiles == TB || (TB == 2 && tiles < 2))
-      evaluate_pass<NS, CH, DT, TB>(data, ln, L, slot, px, c, off, geo, load, sums, fresh);
+    if (tiles != TB && !(TB == 2 && tiles < 2)) return;
+    if constexpr (UNEVEN && TB > 4) {
+      if (rows <= 4)
+        return evaluate_pass<NS, CH, DT, TB, 4>(data, ln, L, slot, px, c, off, geo, load, sums, fresh);
+      if (cols <= 4)
+        return evaluate_pass<NS, CH, DT, 4, TB>(data, ln, L, slot, px, c, off, geo, load, sums, fresh);
+    }
+    evaluate_pass<NS, CH, DT, TB, TB>(data, ln, L, slot, px, c, off, geo, load, sums, fresh);
   });
 }
 
@@ -971,7 +989,7 @@ __device__ __forceinline__ void evaluate_any(const void* data, Shared<NS>& L, in
     const uint32_t geo = L.geo[slot];
     const bool fresh = (geo & kGeoNew) != 0;
     Raw<DT> px[4 * CH][CH];
-    evaluate_four<NS, CH, DT>(data, ln, L, slot, px, Candidate{L.x[slot], L.y[slot], L.hx[slot], L.hy[slot]},
+    evaluate_four<NS, CH, DT, false>(data, ln, L, slot, px, Candidate{L.x[slot], L.y[slot], L.hx[slot], L.hy[slot]},
                               L.off[slot], geo, true, __builtin_amdgcn_ballot_w64(fresh) != 0, fresh);
   }
 }
@@ -1094,7 +1112,7 @@ __device__ __forceinline__ void spread_normal(const Lane& ln, Shared<4>& L, int 
   if (i == 0) L.A[10 + j][slot] = rhs;
 }
 
-template <int NS, int CH, int DT>
+template <int NS, int CH, int DT, bool LONE>
 __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L) {
   constexpr int HM = 16 * CH;
   constexpr bool kKeepA = Shared<NS>::kKeepA;
@@ -1228,8 +1246,9 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         int l = lane;
         // where its registers are short: formed once a step, not held
         if constexpr (CH == 1 || DT != SPOTFIT_U16) asm volatile("" : "+v"(l));
-        evaluate_four<NS, CH, DT>(data, Lane(l), L, own, px, cand, act ? off : __builtin_bit_cast(int64_t, o0),
-                                  act ? geo : geo0, m_new != 0, m_new != 0, fresh);
+        evaluate_four<NS, CH, DT, LONE>(data, Lane(l), L, own, px, cand,
+                                        act ? off : __builtin_bit_cast(int64_t, o0), act ? geo : geo0,
+                                        m_new != 0, m_new != 0, fresh);
       } else {
         wave_lds_sync();
         geo = L.geo[owner ? own : 0];
@@ -1566,11 +1585,16 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
   }
 }
 
-template <int NS, int CH, int DT>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(CH == 1 && (NS == 4 || (NS == 16 && DT == SPOTFIT_U16)) ? 3 : 2))) void fit_matrix_kernel(
+// LONE: a wavefront has a SIMD for itself, and its registers: wide floats of 4 slots,
+// whose pixels take 64 of them, spill none there, and have room for the passes of
+// uneven spots (which cost the others 2 to 6 %).  32 floats of 30x12 32.4 us without
+// it, 24.5 so (26.0 with a lane per column), of 32x32 32.7, 32.4 (30.2).  A batch that
+// needs two wavefronts per SIMD is slower so (10,000 of 32x32 76 us, 118).
+template <int NS, int CH, int DT, bool LONE>
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(LONE ? 1 : CH == 1 && (NS == 4 || (NS == 16 && DT == SPOTFIT_U16)) ? 3 : 2))) void fit_matrix_kernel(
     KArgs /* read through args() */, MatrixQueue mq) {
   __shared__ Shared<NS> lds;
-  fit_matrix<NS, CH, DT>(mq, lds);
+  fit_matrix<NS, CH, DT, LONE>(mq, lds);
 }
 
 __global__ void matrix_queue_reset_kernel(int32_t* take) {
@@ -1579,16 +1603,16 @@ __global__ void matrix_queue_reset_kernel(int32_t* take) {
 
 template <int NS, int CH>
 static const void* symbol(int dtype) {
-  return dtype == SPOTFIT_U16 ? reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_U16>)
-                              : reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_F32>);
+  return dtype == SPOTFIT_U16 ? reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_U16, false>)
+                              : reinterpret_cast<const void*>(&fit_matrix_kernel<NS, CH, SPOTFIT_F32, false>);
 }
 
 template <int NS, int CH>
 static hipError_t launch(const KArgs& ka, const MatrixQueue& mq, int grid, hipStream_t st) {
   if (ka.dtype == SPOTFIT_U16)
-    hipLaunchKernelGGL((fit_matrix_kernel<NS, CH, SPOTFIT_U16>), dim3(grid), dim3(64), 0, st, ka, mq);
+    hipLaunchKernelGGL((fit_matrix_kernel<NS, CH, SPOTFIT_U16, false>), dim3(grid), dim3(64), 0, st, ka, mq);
   else
-    hipLaunchKernelGGL((fit_matrix_kernel<NS, CH, SPOTFIT_F32>), dim3(grid), dim3(64), 0, st, ka, mq);
+    hipLaunchKernelGGL((fit_matrix_kernel<NS, CH, SPOTFIT_F32, false>), dim3(grid), dim3(64), 0, st, ka, mq);
   return hipGetLastError();
 }
 
@@ -1606,7 +1630,7 @@ const void* matrix_kernel_symbol(int slots, bool wide, int dtype) {
 }
 
 hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const MixedWs* ws, int resident,
-                                int spread, hipStream_t st) {
+                                int spread, bool lone, hipStream_t st) {
   const int64_t need = (ka.n + slots - 1) / slots;
   int grid = (int)(need < resident ? need : resident);
   mtx::MatrixQueue mq{};
@@ -1634,6 +1658,10 @@ hipError_t launch_matrix_kernel(int slots, bool wide, const KArgs& ka, const Mix
     if (slots == 4 && spread > 0)
       for (mq.per = 1; mq.per < 4 && (ka.n + mq.per - 1) / mq.per > spread;) mq.per *= 2;
     grid = (int)((ka.n + mq.per - 1) / mq.per);
+  }
+  if (lone && slots == 4 && wide && ka.dtype == SPOTFIT_F32 && !mq.take) {
+    hipLaunchKernelGGL((mtx::fit_matrix_kernel<4, 2, SPOTFIT_F32, true>), dim3(grid), dim3(64), 0, st, ka, mq);
+    return hipGetLastError();
   }
 #define SF_MXLAUNCH(NS, CH) \
   if (slots == NS && wide == (CH == 2)) return mtx::launch<NS, CH>(ka, mq, grid, st);

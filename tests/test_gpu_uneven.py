@@ -38,3 +38,13 @@ def test_small_spots_of_any_shapes(slots, f32):
     ref = _fit(b, 16)
     _equal(_fit(b, slots, max_side=8), ref)
     _equal(_fit(b, slots, schedule=1), ref)
+
+
+@pytest.mark.parametrize("shapes", [[(30, 12)], [(12, 30)], [(20, 16), (29, 7)], [(4, 17), (16, 32)],
+                                    [(30, 12), (12, 30)], [(32, 32), (5, 5)], [(3, 32), (3, 3)]])
+@pytest.mark.parametrize("n", [1, 5, 203])
+def test_a_few_wide_floats(shapes, n):
+    """Spots end at different steps, so that a pass is left with the smaller ones."""
+    _, b, _ = _shapes(shapes, -(-n // len(shapes)), True, seed=n)
+    for schedule in (0, 1):
+        _equal(_fit(b, 4, schedule=schedule), _fit(b, 16, schedule=schedule))
