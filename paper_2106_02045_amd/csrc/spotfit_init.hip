@@ -172,8 +172,8 @@ __device__ __forceinline__ void ring_middle(const uint16_t* px, int w, int h, in
 
 // The spots of a wavefront, up to 64 from `base` on, their descriptions one per
 // lane, and the usable ones in the order in which they are gone through: by the
-// lanes that their larger side takes (8, 16 or 32), whatever sides the launch is
-// for.  100,000 spots of 9x9 with the default options (sides up to 32): moments 45.8
+// lanes that their rows (and, for the moments, whose ring has a lane per column too,
+// their columns) take: 8, 16 or 32, whatever sides the launch is for.  100,000 spots of 9x9 with the default options (sides up to 32): moments 45.8
 // us with groups of 16 lanes and two columns each, 57.6 with 32 lanes for every
 // spot, 23.2 so; brightest-pixel values 24.3, 74.6 and 20.6 (of 7..16 px 20.8 instead
 // of 75; of 17..32 px as before).
@@ -181,11 +181,13 @@ struct Batch {
   spotfit_shape_t sh;  // of spot `base + lane`
   int64_t off;
   bool ok;
+  int cls;       // its class
   int first[4];  // class c (8 << c lanes) is order[first[c]] .. order[first[c + 1] - 1]
 };
 
 // Fills the batch for a kernel of up to LMAX lanes per spot; order: 64 words of LDS.
-template <int LMAX>
+// ROWS: by the rows alone.
+template <int LMAX, bool ROWS>
 __device__ __forceinline__ Batch take_batch(const spotfit_shape_t* sizes, const int64_t* offsets, int64_t base,
                                             int count, int max_side, int max_pixels, int* order) {
   const int lane = __lane_id();
@@ -195,7 +197,7 @@ __device__ __forceinline__ Batch take_batch(const spotfit_shape_t* sizes, const 
     b.off = offsets[base + lane];
   }
   b.ok = lane < count && usable<LMAX>(b.sh, max_side, max_pixels);
-  const int side = b.sh.w > b.sh.h ? b.sh.w : b.sh.h;
+  const int side = !ROWS && b.sh.w > b.sh.h ? b.sh.w : b.sh.h;
   uint64_t m[3];  // the lanes of each class
   m[0] = __builtin_amdgcn_ballot_w64(b.ok && side <= 8);
   m[1] = __builtin_amdgcn_ballot_w64(b.ok && side > 8 && side <= 16);
@@ -213,6 +215,7 @@ __device__ __forceinline__ Batch take_batch(const spotfit_shape_t* sizes, const 
   }
 #pragma unroll
   for (int c = 0; c < 3; ++c) {
+    if (m[c] >> lane & 1) b.cls = c;
     if (m[c] >> lane & 1)
       order[b.first[c] + (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m[c] >> 32),
                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)m[c], 0u))] = lane;
@@ -227,10 +230,11 @@ __device__ __forceinline__ int pick(int v, int lane) { return __builtin_amdgcn_d
 // f(windows, from, valid, w, h, pixels) for the spots of the batch that take L
 // lanes, 64 / L at a time: `from` the lane that describes the spot of this lane's
 // group (the last one again where there are no more: not valid).  Rows are gone
-// through in L / 4 windows of 4 columns; with 32 lanes in 6 where no spot has more
-// than 24 columns, 58 us instead of 75 for the brightest-pixel values of
-// 100,000 spots of 17x17.
-template <int L, typename F>
+// through in L / 4 windows of 4 columns, or LMAX / 4 where a spot has more columns
+// than L; with 32 lanes in 6 where no spot has more than 24 columns, 58 us instead
+// of 75 for the brightest-pixel values of 100,000 spots of 17x17.  Of 30x12 (w x h),
+// by their larger side 73 us, by their rows 36 (54 before the row kernels).
+template <int L, int LMAX, typename F>
 __device__ __forceinline__ void for_spots(const Batch& b, const uint16_t* data, const int* order, F&& f) {
   constexpr int C = L == 8 ? 0 : L == 16 ? 1 : 2, G = 64 / L;
   const int begin = b.first[C], end = b.first[C + 1];
@@ -247,8 +251,11 @@ __device__ __forceinline__ void for_spots(const Batch& b, const uint16_t* data, 
       f(windows, from, i + g < end, wh & 0xff, wh >> 8, data + o);
     }
   };
+  auto wider = [&](int w) { return __builtin_amdgcn_ballot_w64(b.ok && b.cls == C && b.sh.w > w) != 0; };
   if constexpr (L == 32) {
-    if (__builtin_amdgcn_ballot_w64(b.ok && b.sh.w > 24) == 0) return go(std::integral_constant<int, 6>{});
+    if (!wider(24)) return go(std::integral_constant<int, 6>{});
+  } else if constexpr (LMAX > L) {
+    if (wider(L)) return go(std::integral_constant<int, LMAX / 4>{});
   }
   go(std::integral_constant<int, L / 4>{});
 }
@@ -263,7 +270,7 @@ template <int L>
 __device__ __forceinline__ void moment_rows(const Batch& b, const uint16_t* data, const int* order, double* sxx,
                                             double* syy, uint32_t* s0, uint32_t* sx, uint32_t* sy) {
   const int r = __lane_id() % L;
-  for_spots<L>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
+  for_spots<L, L>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
     constexpr int W = decltype(windows)::value;
     Row<W> row;
     load_row<W>(px, w, h, r, row);
@@ -303,7 +310,7 @@ __global__ __launch_bounds__(64) void moment_rows_kernel(const uint16_t* data, c
   const int lane = __lane_id();
   const int64_t base = (int64_t)blockIdx.x * per_block;
   const int count = n - base < per_block ? (int)(n - base) : per_block;
-  const Batch b = take_batch<LMAX>(sizes, offsets, base, count, max_side, max_pixels, order);
+  const Batch b = take_batch<LMAX, false>(sizes, offsets, base, count, max_side, max_pixels, order);
   const spotfit_shape_t sh = b.sh;
   const bool ok = b.ok;
   moment_rows<8>(b, data, order, sxx, syy, s0, sx, sy);
@@ -338,11 +345,11 @@ __global__ __launch_bounds__(64) void moment_rows_kernel(const uint16_t* data, c
 // rounded quotients do; with 31 - column below it, a row's largest such number is
 // its first brightest window.  Measured: 1M spots of 15x15 in 0.188 ms instead
 // of 0.79, of 32x32 in 0.67 instead of 1.50.
-template <int L>
+template <int L, int LMAX>
 __device__ __forceinline__ void peak_rows(const Batch& b, const uint16_t* data, const int* order,
                                           uint32_t* where, uint32_t* area) {
   const int r = __lane_id() % L;
-  for_spots<L>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
+  for_spots<L, LMAX>(b, data, order, [&](auto windows, int from, bool valid, int w, int h, const uint16_t* px) {
     constexpr int W = decltype(windows)::value;
     Row<W> row;
     load_row<W>(px, w, h, r, row);
@@ -412,11 +419,11 @@ __global__ __launch_bounds__(64) void peak_rows_kernel(const uint16_t* data, con
   const int lane = __lane_id();
   const int64_t base = (int64_t)blockIdx.x * per_block;
   const int count = n - base < per_block ? (int)(n - base) : per_block;
-  const Batch b = take_batch<LMAX>(sizes, offsets, base, count, max_side, max_pixels, order);
+  const Batch b = take_batch<LMAX, true>(sizes, offsets, base, count, max_side, max_pixels, order);
   const bool ok = b.ok;
-  peak_rows<8>(b, data, order, where, area);
-  if constexpr (LMAX >= 16) peak_rows<16>(b, data, order, where, area);
-  if constexpr (LMAX >= 32) peak_rows<32>(b, data, order, where, area);
+  peak_rows<8, LMAX>(b, data, order, where, area);
+  if constexpr (LMAX >= 16) peak_rows<16, LMAX>(b, data, order, where, area);
+  if constexpr (LMAX >= 32) peak_rows<32, LMAX>(b, data, order, where, area);
   __syncthreads();
   if (lane < count) {
     const float nanf = __builtin_nanf("");
