@@ -572,9 +572,16 @@ template <int L>
 hipError_t launch_rows(int method, const uint16_t* data, const spotfit_shape_t* sizes, const int64_t* offsets,
                        int64_t n, int max_side, int max_pixels, float* out, hipStream_t st) {
   // up to 64 spots per wavefront, fewer where that leaves the chip idle (16
-  // wavefronts per CU on 256 CUs)
+  // wavefronts per CU on 256 CUs); a launch takes fewer than 2^32 threads
   int per = 64;
   while (per > 64 / L && n < (int64_t)per * 4096) per /= 2;
+  constexpr int64_t kSpots = (int64_t)1 << 30;
+  if (n > kSpots) {
+    const hipError_t e = launch_rows<L>(method, data, sizes, offsets, kSpots, max_side, max_pixels, out, st);
+    return e != hipSuccess ? e
+                           : launch_rows<L>(method, data, sizes + kSpots, offsets + kSpots, n - kSpots, max_side,
+                                            max_pixels, out + 4 * kSpots, st);
+  }
   const int64_t blocks = (n + per - 1) / per;
   if (method == kInitMoments)
     hipLaunchKernelGGL((ini::moment_rows_kernel<L>), dim3((unsigned)blocks), dim3(64), 0, st, data, sizes,
