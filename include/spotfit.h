@@ -256,7 +256,8 @@ int spotfit_peak_init(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
  * init_out float[n][4] (device, caller-owned, required) receives the start
  * values each fit began from (NaN for the shapes spotfit_moment_init rejects,
  * whose fits end as BAD_INPUT).  They equal spotfit_moment_init's (with such
- * other plans: up to the order of its double-precision sums), and the fit
+ * other plans, and for floats with SPOTFIT_PLAN_LATENCY: up to the order of its
+ * double-precision sums), and the fit
  * outputs are bit for bit those of spotfit_fit_spots with init = init_out and
  * the same plan.  The other arguments, ownership,
  * stream and return codes as spotfit_fit_spots. */

@@ -539,7 +539,8 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
     const bool mixed = o.schedule == SPOTFIT_SCHEDULE_MIXED;
     if (init_out) {
       e = sf::launch_start_values(sf::kInitMoments, data, dtype, sizes, offsets, n, o.max_side,
-                                  o.max_pixels, init_out, (hipStream_t)stream);
+                                  o.max_pixels, init_out, (hipStream_t)stream,
+                                  o.plan_hint == SPOTFIT_PLAN_LATENCY);
       if (e != hipSuccess) return fail_hip(e, "start-value kernel launch");
       ka.init = init_out;
       ka.init_out = nullptr;

@@ -154,10 +154,12 @@ hipError_t launch_classify(const KArgs& ka, const MixedWs& ws, hipStream_t st);
 // Start values from the pixels for spots with sides up to max_side: float[n][4]
 // into out.  kInitMoments: centroid / second moments; kInitPeak: the paper's
 // recipe (brightest pixel of the 3 x 3 moving average, sigma = sqrt(M / pi)).
+// lane_per_column: the moments of floats by a lane per column, soonest for a few
+// spots, their double-precision sums in another order.
 enum { kInitMoments = 0, kInitPeak = 1 };
 hipError_t launch_start_values(int method, const void* data, int dtype, const spotfit_shape_t* sizes,
                                const int64_t* offsets, int64_t n, int max_side, int max_pixels,
-                               float* out, hipStream_t st);
+                               float* out, hipStream_t st, bool lane_per_column = false);
 
 // Up to kCopyMax arrays to copy with one kernel launch, kCopyBytes at most in
 // all (there the engine's hand-over still costs a fifth more): `add` takes one if
