@@ -280,7 +280,7 @@ typedef struct {
 /* Summarise the device arrays status[n], iters[n] and evals[n][2] (evals may be
  * NULL) of a fit enqueued earlier on `stream`: a histogram kernel runs on the
  * stream, then the call waits for the stream and fills *out (host).  Uses a
- * buffer the context owns.  Returns SPOTFIT_OK, SPOTFIT_E_NULL, SPOTFIT_E_ARG
+ * buffer the context owns, allocated by its first such call.  Returns SPOTFIT_OK, SPOTFIT_E_NULL, SPOTFIT_E_ARG
  * (n < 0) or SPOTFIT_E_HIP. */
 int spotfit_get_stats(spotfit_ctx_t* ctx, const int32_t* status, const int32_t* iters,
                       const int32_t* evals, int64_t n_spots, spotfit_stats_t* out, void* stream);

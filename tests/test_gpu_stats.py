@@ -29,3 +29,20 @@ def test_counts_match_numpy(n, with_evals):
         for i, k in enumerate(("grad_evals", "trial_evals")):
             want = int(np.maximum(out["evals"][:, i].astype(np.int64), 0).sum()) if with_evals else 0
             assert st[k] == want
+
+
+def test_contexts_take_turns():
+    """Every context has its own counts, whether it is the first call on it or not, and
+    one that never counted is destroyed like the others."""
+    import torch
+
+    import paper_2106_02045_amd as sf
+    dev = [{"status": torch.full((k + 1,), k, dtype=torch.int32, device="cuda:0"),
+            "iters": torch.full((k + 1,), 10 * k, dtype=torch.int32, device="cuda:0")} for k in range(3)]
+    ctx = [sf.Context(0) for _ in range(4)]
+    for _ in range(2):
+        for k in range(3):
+            st = ctx[k].stats(dev[k])
+            assert st["n_spots"] == k + 1 and st["status_count"][k] == k + 1 and st["iters_hist"][10 * k] == k + 1
+    for c in ctx:
+        c.close()
