@@ -424,10 +424,6 @@ int check_mixed_count(const spotfit_options_t& o, int64_t n, const char* who) {
   return SPOTFIT_OK;
 }
 
-// Largest batch for which the latency hint takes the one-wave-per-SIMD build
-// of the wide mixed-size plan (measured: faster up to 40,000 spots of the
-// serving and mixed workloads, slower from 400,000).
-constexpr int64_t kLeanMaxSpots = 65536;
 // The lane-owned plans hold 16-64 spots per wavefront and make a pass per
 // spot of a group each step: they pay off when every resident spot slot fits
 // several spots in turn; a smaller batch takes the narrow plan of the same
@@ -451,8 +447,9 @@ constexpr int64_t kOwnedMinSpotsPerLane = 4;
 // 395, 200,000 486 / 503; 400,000 970 / 959, 2M 3723 / 3185).
 constexpr int64_t kMatrixUnsorted = 262144;
 
-// Whether a fit with these options runs the matrix-core kernel: both plan hints,
-// unless an override or the autotuner chose another plan.
+// Whether a fit with these options runs the matrix-core kernel: always with the
+// latency hint, and otherwise unless an override or the autotuner chose another
+// plan.
 bool takes_matrix(const spotfit_ctx_t* ctx, const spotfit_options_t& o) {
   if (o.precision != SPOTFIT_PREC_FP64) return false;
   if (o.plan_hint == SPOTFIT_PLAN_LATENCY) return true;
@@ -589,11 +586,7 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
                            : own_ws   ? *own_ws
                                       : sf::MixedWs{ctx->ws, ctx->ws + sf::kMixedHeadWords, ctx->ws_cap,
                                                     ctx->ws + 8};
-    // latency: the wide mixed-size plan (8, 16, 32 lanes per spot); up to
-    // kLeanMaxSpots spots its one-wave-per-SIMD build, which spills no
-    // registers (those batches leave most of the chip idle anyway)
-    int mplan = o.plan_hint == SPOTFIT_PLAN_LATENCY ? (n <= kLeanMaxSpots ? 3 : 0)
-                                                    : ctx->mixed_plan;
+    int mplan = ctx->mixed_plan;
     if (sf::mixed_plan_narrow(mplan) != mplan && !ctx->mixed_forced &&
         n < kOwnedMinSpotsPerLane * (int64_t)ctx->n_cu * ctx->occ_mixed[mplan] * 64)
       mplan = sf::mixed_plan_narrow(mplan);
@@ -604,12 +597,6 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
                    : sf::launch_mixed(mplan, ka, ws, grid, (hipStream_t)stream);
   } else if (o.precision == SPOTFIT_PREC_FP64) {
     const int cls = o.max_side <= 8 ? 0 : o.max_side <= 16 ? 1 : 2;
-    // latency: the wide plans with one lane per column (8x1, 16x1, 32x1); the
-    // builds of 16x1 and 32x1 that spill no registers for batches that they hold
-    // resident at once (measured: up to 5-10 % faster there, 10-35 % slower at
-    // several resident rounds)
-    const int one_wave = sf::wide_plan_count() + sf::narrow_plan_count();
-    const int wide_for_class[3] = {0, 2, 4}, lean_for_class[3] = {0, one_wave, one_wave + 1};
     int plan = ctx->plan_for_class[cls];
     if (sf::plan_for_raw(plan) != plan) {  // a lane-owned plan
       int ol = 0, oc = 0;
@@ -619,12 +606,6 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
         plan = sf::plan_for_raw(plan);
     }
     int lanes = 0, cpl = 0;
-    if (o.plan_hint == SPOTFIT_PLAN_LATENCY) {
-      plan = wide_for_class[cls];
-      const int lean = lean_for_class[cls];
-      sf::group_plan_shape(lean, &lanes, &cpl);
-      if (lean != plan && n <= (int64_t)ctx->n_cu * ctx->occ_plan[lean] * (64 / lanes)) plan = lean;
-    }
     sf::group_plan_shape(plan, &lanes, &cpl);
     const int64_t per_wave = 64 / lanes;
     const int64_t need = (n + per_wave - 1) / per_wave;
@@ -665,7 +646,7 @@ int launch_fit(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
 // Whether a fit of n spots with start values in memory (validated options o)
 // takes a lane-owned plan: the plan choice of launch_fit.
 bool takes_owned(const spotfit_ctx_t* ctx, int64_t n, const spotfit_options_t& o) {
-  if (o.precision != SPOTFIT_PREC_FP64 || o.plan_hint == SPOTFIT_PLAN_LATENCY) return false;
+  if (o.precision != SPOTFIT_PREC_FP64) return false;
   if (o.schedule == SPOTFIT_SCHEDULE_MIXED) {
     const int mplan = ctx->mixed_plan;
     return sf::mixed_plan_narrow(mplan) != mplan &&
