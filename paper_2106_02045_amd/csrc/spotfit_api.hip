@@ -687,16 +687,21 @@ int launch_raw(spotfit_ctx_t* ctx, const void* data, int32_t dtype, const spotfi
 
 namespace sf {
 
+bool reads_class_lists(const spotfit_ctx_t* ctx, int64_t n, const spotfit_options_t& o) {
+  return o.precision == SPOTFIT_PREC_FP64 && o.schedule == SPOTFIT_SCHEDULE_MIXED &&
+         (!takes_matrix(ctx, o) || n > kMatrixUnsorted);
+}
+
 int fit_preclassified(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
                       const spotfit_shape_t* sizes, const int64_t* offsets, const float* init,
-                      float* init_out, int64_t n, const spotfit_options_t& o, const MixedWs& ws,
+                      float* init_out, int64_t n, const spotfit_options_t& o, const MixedWs* ws,
                       float* params_out, float* chi2_out, int32_t* iters_out, int32_t* status_out,
                       void* stream) {
   if (o.precision != SPOTFIT_PREC_FP64 || o.schedule != SPOTFIT_SCHEDULE_MIXED)
     return fail(SPOTFIT_E_OPTIONS, "fit_preclassified: double precision, mixed schedule only");
   if (n == 0) return SPOTFIT_OK;
   return launch_fit(ctx, data, dtype, sizes, offsets, init_out ? nullptr : init, n, o, params_out,
-                    chi2_out, iters_out, status_out, nullptr, stream, init_out, &ws);
+                    chi2_out, iters_out, status_out, nullptr, stream, init_out, ws);
 }
 
 }  // namespace sf

@@ -85,15 +85,19 @@ hipError_t launch_mixed(int plan, const KArgs& ka, const MixedWs& ws, int grid, 
 // and counts (taken counters zero), without the classify pass.
 hipError_t launch_mixed_fit(int plan, const KArgs& ka, const MixedWs& ws, int grid, hipStream_t st);
 
+// Whether a fit of n spots with these (validated) options on this context goes
+// through the class lists of the mixed schedule.
+bool reads_class_lists(const spotfit_ctx_t* ctx, int64_t n, const spotfit_options_t& o);
+
 // A fit of spots whose size classes the caller listed (options validated,
-// double precision, mixed schedule): ws.counters[0..2] the class sizes,
-// ws.counters[3..5] zero, class c's spot indices at ws.lists + c * ws.cap, all
-// in device memory.  init_out not NULL: start values computed in the launch
-// and written there (init unused), as spotfit_fit_raw.  One launch, no
+// double precision, mixed schedule): ws->counters[0..2] the class sizes,
+// ws->counters[3..5] zero, class c's spot indices at ws->lists + c * ws->cap, all
+// in device memory; ws null where reads_class_lists says no.  init_out not NULL:
+// start values computed and written there (init unused), as spotfit_fit_raw.  No
 // classify pass.  Returns SPOTFIT_OK or a negative spotfit_error_t.
 int fit_preclassified(spotfit_ctx_t* ctx, const void* data, int32_t dtype,
                       const spotfit_shape_t* sizes, const int64_t* offsets, const float* init,
-                      float* init_out, int64_t n, const spotfit_options_t& o, const MixedWs& ws,
+                      float* init_out, int64_t n, const spotfit_options_t& o, const MixedWs* ws,
                       float* params_out, float* chi2_out, int32_t* iters_out, int32_t* status_out,
                       void* stream);
 

@@ -55,6 +55,7 @@ struct FrameRec {
   int state = kFree;
   int dtype = 0;
   bool dev_init = false;   // start values computed on the device
+  bool lists = false;      // class lists came along
   int64_t n = 0;           // spots
   int64_t spot0 = 0;       // first index in the spot ring
   int64_t pix_off = 0;     // byte offset in the pixel ring
@@ -181,10 +182,13 @@ hipError_t alloc_host(T** h, int64_t n) {
 
 // A frame's own records, staged right after its pixels in the pixel ring so that
 // a batch of one frame moves them in with its pixels: offsets (8 B per spot),
-// shapes (4 B), start values (16 B, after 4 B of padding), the size-class lists
-// (3 x 4 B: class c's spot indices from c * n) and the eight counters of a
-// mixed-size launch (class sizes, then zeros).
-int64_t frame_meta_bytes(int64_t n) { return n > 0 ? (44 * n + 32 + 255) & ~(int64_t)255 : 0; }
+// shapes (4 B), start values (16 B, after 4 B of padding) and, for a fit that goes
+// through them (a very large frame, or another mapping by an override), the
+// size-class lists (3 x 4 B: class c's spot indices from c * n) and the eight
+// counters of a mixed-size launch (class sizes, then zeros).
+int64_t frame_meta_bytes(int64_t n, bool lists) {
+  return n > 0 ? ((lists ? 44 * n + 32 : 32 * n) + 255) & ~(int64_t)255 : 0;
+}
 
 struct FrameMeta {
   int64_t* offs;
@@ -315,15 +319,16 @@ bool spotfit_serve::launch_ready() {
   const BatchView dv = batch_view(d_meta + kMetaBytes * spot0, d_res + kResBytes * spot0, nsp);
   int rc = SPOTFIT_OK;
   if (t1 == t0 + 1 && opt.precision == SPOTFIT_PREC_FP64 && opt.schedule == SPOTFIT_SCHEDULE_MIXED) {
-    // one frame: its records and class lists came in with its pixels, and the
-    // fit starts without a classify pass: two API calls fewer per frame, which
-    // the dispatcher thread otherwise spends while the GPU waits
+    // one frame: its records (and class lists, if the fit reads any) came in with
+    // its pixels, and the fit starts without a classify pass: fewer API calls per
+    // frame, which the dispatcher thread otherwise spends while the GPU waits
     const FrameMeta m = frame_meta(d_pix + rec(t0).meta_off, nsp);
     const sf::MixedWs ws{m.counters, m.lists, nsp};
     if (e == hipSuccess) e = sf::launch_copy(list, st);
     if (e == hipSuccess)
       rc = sf::fit_preclassified(ctxs[si], d_pix, dtype, m.sizes, m.offs, dev_init ? nullptr : m.init,
-                                 dev_init ? m.init : nullptr, nsp, opt, ws, dv.params, dv.chi2,
+                                 dev_init ? m.init : nullptr, nsp, opt, rec(t0).lists ? &ws : nullptr,
+                                 dv.params, dv.chi2,
                                  dv.iters, dv.status, st);
   } else {
     // the batch's records, packed on the host into its meta slice: one copy (the
@@ -335,7 +340,7 @@ bool spotfit_serve::launch_ready() {
     if (e == hipSuccess && !list.add(d_meta + kMetaBytes * spot0, m_meta + kMetaBytes * spot0, bytes))
       e = hipMemcpyAsync(dv.offs, hv.offs, (size_t)bytes, hipMemcpyHostToDevice, st);
     if (e == hipSuccess) e = sf::launch_copy(list, st);
-    if (e == hipSuccess && dev_init)  // start values on the device, in the fit's own launch
+    if (e == hipSuccess && dev_init)  // start values on the device
       rc = spotfit_fit_raw(ctxs[si], d_pix, dtype, dv.sizes, dv.offs, nsp, &opt, dv.init,
                            dv.params, dv.chi2, dv.iters, dv.status, nullptr, st);
     else if (e == hipSuccess)
@@ -623,7 +628,8 @@ int spotfit_serve_submit(spotfit_serve_t* sv, const spotfit_frame_t* fr, uint64_
   int64_t npx = 0;
   for (int64_t i = 0; i < n; ++i) npx += (int64_t)fr->sizes[i].w * fr->sizes[i].h;
   const int64_t px_bytes = ((npx * esz) + 255) & ~(int64_t)255;
-  const int64_t bytes = px_bytes + frame_meta_bytes(n);
+  const bool lists = sf::reads_class_lists(sv->ctxs[0], n, sv->opt);  // all contexts alike
+  const int64_t bytes = px_bytes + frame_meta_bytes(n, lists);
   std::unique_lock<std::mutex> lk(sv->mu);
   if (fr->drift_out && (sv->track_markers == 0 || n != sv->track_markers))
     return serve_fail(SPOTFIT_E_ARG, "serve_submit: a tracked frame needs tracking on and one spot per marker");
@@ -646,6 +652,7 @@ int spotfit_serve_submit(spotfit_serve_t* sv, const spotfit_frame_t* fr, uint64_
   f.ticket = t;
   f.dtype = fr->dtype;
   f.dev_init = fr->init == nullptr;
+  f.lists = lists;
   f.n = n;
   f.spot0 = sv->spot_head;
   f.pix_off = sv->pix_head;
@@ -682,12 +689,14 @@ int spotfit_serve_submit(spotfit_serve_t* sv, const spotfit_frame_t* fr, uint64_
     std::memcpy(m.offs, sv->h_offs + f.spot0, sizeof(int64_t) * n);
     std::memcpy(m.sizes, fr->sizes, sizeof(spotfit_shape_t) * n);
     if (fr->init) std::memcpy(m.init, fr->init, sizeof(float) * 4 * n);
-    int32_t cnt[3] = {0, 0, 0};
-    for (int64_t i = 0; i < n; ++i) {
-      const int c = size_class_of(fr->sizes[i]);
-      m.lists[c * n + cnt[c]++] = (int32_t)i;
+    if (lists) {
+      int32_t cnt[3] = {0, 0, 0};
+      for (int64_t i = 0; i < n; ++i) {
+        const int c = size_class_of(fr->sizes[i]);
+        m.lists[c * n + cnt[c]++] = (int32_t)i;
+      }
+      for (int c = 0; c < 8; ++c) m.counters[c] = c < 3 ? cnt[c] : 0;
     }
-    for (int c = 0; c < 8; ++c) m.counters[c] = c < 3 ? cnt[c] : 0;
   }
   if (sv->t_first == 0) sv->t_first = f.t_arrival;
   sv->next_ticket = t + 1;
