@@ -65,6 +65,13 @@ def measured_traffic(workload: str, precision: str, schedule: str):
     return t["hbm_bytes_per_launch"]
 
 
+def vector_pipe_cycles(cnt) -> float:
+    """Cycles of the vector pipes for these counters: 16 per double-precision matrix
+    instruction (SQ_INSTS_VALU counts them too), 4 per other vector instruction."""
+    mfma = cnt.get("SQ_INSTS_MFMA", 0)
+    return (cnt["SQ_INSTS_VALU"] - mfma) * 4 + mfma * 16
+
+
 def measured_counters(workload: str, precision: str, schedule: str):
     """Per-launch hardware counters of the fit kernel from the committed summary
     (rocprofv3 --pmc over one launch), or None when no summary exists for this
@@ -281,15 +288,15 @@ def main():
                  "alone_vs_mix_differing": sv["alone_vs_mix"]["frames_differing"]}
 
     # issue utilisation from the hardware counters of one launch of this kernel
-    # build (committed summary, stamped with the sources' hash): VALU wave
-    # instructions x 4 cycles over the SIMD cycles of the measured launch time
+    # build (committed summary, stamped with the sources' hash): the vector pipe's
+    # cycles over the SIMD cycles of the measured launch time
     valu = None
     cnt = measured_counters(a.workload, a.precision, a.schedule)
     if cnt is not None:
         simd_cycles = 256 * 4 * CLOCK_HZ * k_avg_s
         f64 = cnt["SQ_INSTS_VALU_FMA_F64"] * 2 + cnt["SQ_INSTS_VALU_MUL_F64"] + \
             cnt["SQ_INSTS_VALU_ADD_F64"] + 8 * cnt.get("SQ_INSTS_MFMA", 0)  # 512 flop each, per lane
-        valu = {"issue_frac": cnt["SQ_INSTS_VALU"] * 4 / simd_cycles,
+        valu = {"issue_frac": vector_pipe_cycles(cnt) / simd_cycles,
                 "fp64_flop_frac": f64 * 64 / k_avg_s / (PEAK_ALU_TFLOPS * 1e12),
                 "valu_insts_per_launch": cnt["SQ_INSTS_VALU"],
                 "fp64_flops_per_launch": f64 * 64,
