@@ -107,7 +107,7 @@ typedef enum {
 } spotfit_schedule_t;
 
 /* Which mapping the double-precision kernel uses.  Both hints run the matrix-core
- * kernel, with 4, 16 or 64 spots per wavefront by the size of the batch: 4 for
+ * kernel, with 4, 16, 32 or 64 spots per wavefront by the size of the batch: 4 for
  * the shortest steps (a camera frame), 64 for the most spots per second.  A
  * spot's result does not depend on that, nor on the batch it is in. */
 typedef enum {

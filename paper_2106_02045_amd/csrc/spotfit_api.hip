@@ -36,7 +36,7 @@ struct spotfit_ctx {
   int32_t* ws;      // counters[8] then 3 lists of ws_cap spot indices
   int64_t ws_cap;
   void* stats;  // host memory that the blocks of spotfit_get_stats write, from its first call on
-  int32_t* queue;             // spot counter of the narrow kernel's uniform launches
+  int32_t* queue;             // the launches' spot counters
   int32_t* scratch;           // device address of this device's copy of `scratch` (below)
 };
 
@@ -473,8 +473,14 @@ int64_t matrix_resident(const spotfit_ctx_t* ctx, int slots_index, int32_t dtype
 //   21 px     8,000: 54 / 67 / 94 / 145   32,000: 149 / 98 / 97 / 149    65,000: 274 / 198 / 147 / 153
 //   32 px     8,000: 71 / 94 / 134 / 217  65,000: 367 / 267 / 202 / 224 100,000: 534 / 379 / 343 / 351
 //   7..32 px  8,000: 54 / 80 / 115 / 190  65,000: 321 / 249 / 188 / 211 130,000: 600 / 414 / 387 / 320
-// Wide floats, whose products wait longer for their pixels, keep 4 spots a
-// little further (17 px, 12,000: 73 / 97; 16,000: 91 / 98).
+// Wide floats, whose products wait longer for their pixels, keep 4 spots for half
+// as many more (4 / 16 spots, 10,000 and 12,288: 17 px 54 / 63, 70 / 64; 24 px 59 /
+// 74, 77 / 79; 32 px 77 / 99, 94 / 100; 7..32 px 78 / 95, 96 / 97; 16,384 of 28 px 97
+// / 87).  Large batches of floats of 29..32 px are the one kind that the lane-owned
+// mapping fits sooner (100,000 of 32x32 538 us, 565 here; 1M 4.05 ms, 4.92; of 17 px
+// 1.55 ms for 400,000, 1.05 here): the second pass of a step over the pixels, for the
+// residuals.  max_side cannot tell, since 32 is its default, and a spot's bits are not
+// to depend on its batch; spotfit_autotune finds it.
 int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, int32_t dtype, const spotfit_options_t& o) {
   int64_t most[kMatrixBuilds - 1];
   for (int i = 0; i < kMatrixBuilds - 1; ++i)
@@ -488,8 +494,8 @@ int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, int32_t dtype, const 
 }
 
 // Enqueue one fit with validated options o and n > 0.  init_out not NULL (with
-// init NULL): the separable double-precision kernels compute the start values
-// themselves and write them there.  Mixed schedule: `classified` is a
+// init NULL, double precision): start values are computed, in a launch before the
+// fit's or by the narrow and wide plans in theirs, and written there.  Mixed schedule: `classified` is a
 // workspace whose class lists are already built (no classify pass); otherwise
 // `own_ws` (not NULL: a workspace of at least n spots that the caller owns) or
 // the context's workspace, grown to n spots if needed, takes the classify pass.

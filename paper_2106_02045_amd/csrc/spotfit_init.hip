@@ -26,7 +26,7 @@ namespace ini {
 using namespace lg;
 
 template <int L, int CPL>
-__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void moment_init_kernel(const void* data, int dtype,
+__global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void moment_init_kernel(const float* data,
                                                          const spotfit_shape_t* sizes,
                                                          const int64_t* offsets, int64_t n,
                                                          int max_side, int max_pixels,
@@ -42,7 +42,7 @@ __global__ __launch_bounds__(64) __attribute__((amdgpu_waves_per_eu(4))) void mo
       continue;
     }
     float o[4];
-    moment_init_spot<L, CPL>(data, dtype, sh, offsets[s], li, o);
+    moment_init_spot<L, CPL>(data, SPOTFIT_F32, sh, offsets[s], li, o);
     if (li == 0)
       for (int q = 0; q < 4; ++q) out[4 * s + q] = o[q];
   }
@@ -442,11 +442,11 @@ __global__ __launch_bounds__(64) void peak_rows_kernel(const uint16_t* data, con
 }
 
 // ---------------------------------------------------------------------------
-// The paper's start values.  Per own pixel the 3 x 3 window sum is formed in
+// The paper's start values of float pixels.  Per own pixel the 3 x 3 window sum is formed in
 // double from the pixel's column and its two neighbours (clamped loads, masked
 // outside the ROI) and divided by the number of in-ROI window pixels; the sums
-// are exact for 16-bit pixels (and for 32-bit float pixels within 2^26 of each
-// other), so their order does not matter.  The group keeps the largest mean
+// are exact for pixels within 2^26 of each other, so their order does not matter
+// there.  The group keeps the largest mean
 // and, among equal means, the smallest row-major index.
 // ---------------------------------------------------------------------------
 template <int L>
@@ -477,7 +477,7 @@ __device__ __forceinline__ float gmax_f(float v) {
 }
 
 template <int L, int CPL>
-__global__ __launch_bounds__(64) void peak_init_kernel(const void* data, int dtype,
+__global__ __launch_bounds__(64) void peak_init_kernel(const float* data,
                                                        const spotfit_shape_t* sizes,
                                                        const int64_t* offsets, int64_t n,
                                                        int max_side, int max_pixels, float* out) {
@@ -507,9 +507,9 @@ __global__ __launch_bounds__(64) void peak_init_kernel(const void* data, int dty
 #pragma unroll
       for (int r = 0; r < HM; ++r) {
         const int64_t row = off + (int64_t)(r < h ? r : h - 1) * w;
-        g0[r] = load_px(data, dtype, row + cm);
-        g1[r] = load_px(data, dtype, row + cc);
-        g2[r] = load_px(data, dtype, row + cp);
+        g0[r] = data[row + cm];
+        g1[r] = data[row + cc];
+        g2[r] = data[row + cp];
       }
       const bool left = c >= 1, right = c + 1 < w;
       const int ncol = 1 + (left ? 1 : 0) + (right ? 1 : 0);
@@ -550,7 +550,7 @@ __global__ __launch_bounds__(64) void peak_init_kernel(const void* data, int dty
       if (c >= w) continue;
 #pragma unroll
       for (int r = 0; r < HM; ++r)
-        if (r < h) m += double(load_px(data, dtype, off + (int64_t)r * w + c)) > thr ? 1 : 0;
+        if (r < h) m += double(data[off + (int64_t)r * w + c]) > thr ? 1 : 0;
     }
     m = gsum_i<L>(m);
     double sig = sqrt(double(m) / kPi);
@@ -593,16 +593,16 @@ hipError_t launch_rows(int method, const uint16_t* data, const spotfit_shape_t* 
 }
 
 template <int L, int CPL>
-hipError_t launch_streamed(int method, const void* data, const spotfit_shape_t* sizes, const int64_t* offsets,
+hipError_t launch_streamed(int method, const float* data, const spotfit_shape_t* sizes, const int64_t* offsets,
                            int64_t n, int max_side, int max_pixels, float* out, hipStream_t st) {
   int64_t blocks = (n + 64 / L - 1) / (64 / L);
   blocks = blocks < (1 << 20) ? blocks : (1 << 20);  // the kernels stride over the rest
   if (method == kInitMoments)
     hipLaunchKernelGGL((ini::moment_init_kernel<L, CPL>), dim3((unsigned)blocks), dim3(64), 0, st, data,
-                       SPOTFIT_F32, sizes, offsets, n, max_side, max_pixels, out);
+                       sizes, offsets, n, max_side, max_pixels, out);
   else
     hipLaunchKernelGGL((ini::peak_init_kernel<L, CPL>), dim3((unsigned)blocks), dim3(64), 0, st, data,
-                       SPOTFIT_F32, sizes, offsets, n, max_side, max_pixels, out);
+                       sizes, offsets, n, max_side, max_pixels, out);
   return hipGetLastError();
 }
 
@@ -617,18 +617,19 @@ hipError_t launch_start_values(int method, const void* data, int dtype, const sp
     if (max_side <= 16) return launch_rows<16>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
     return launch_rows<32>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
   }
+  const float* px = static_cast<const float*>(data);
   // a lane per column for the latency hint (raw floats with the fit, us with groups of 4
   // or 16 lanes / so: 32 of 15x15 35.0 / 25.1, of 32x32 37.7 / 33.9; 10,000 of 15x15
   // 51 / 42, 100,000 228 / 194)
   if (lane_per_column && method == kInitMoments) {
-    if (max_side <= 8) return launch_streamed<8, 1>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
-    if (max_side <= 16) return launch_streamed<16, 1>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
-    return launch_streamed<32, 1>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
+    if (max_side <= 8) return launch_streamed<8, 1>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
+    if (max_side <= 16) return launch_streamed<16, 1>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
+    return launch_streamed<32, 1>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
   }
   // float pixels: groups of 4 lanes (2 or 4 columns each) up to 16 pixels a side, 16 beyond
-  if (max_side <= 8) return launch_streamed<4, 2>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
-  if (max_side <= 16) return launch_streamed<4, 4>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
-  return launch_streamed<16, 2>(method, data, sizes, offsets, n, max_side, max_pixels, out, st);
+  if (max_side <= 8) return launch_streamed<4, 2>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
+  if (max_side <= 16) return launch_streamed<4, 4>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
+  return launch_streamed<16, 2>(method, px, sizes, offsets, n, max_side, max_pixels, out, st);
 }
 
 }  // namespace sf

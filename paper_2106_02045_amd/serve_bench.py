@@ -48,7 +48,7 @@ def run(argv=None) -> dict:
     ap.add_argument("--check", type=int, default=200, help="frames compared with a direct fit")
     ap.add_argument("--seed", type=int, default=4)
     ap.add_argument("--plan", default="latency", choices=["latency", "throughput"],
-                    help="lane mapping of the fit (latency: one lane per column)")
+                    help="plan hint of the fit (latency: never another mapping than the default one)")
     ap.add_argument("--device-init", action="store_true",
                     help="frames carry no start values: the loop computes them on the device")
     ap.add_argument("--track", type=int, default=0, help="markers per frame of a tracked sample")

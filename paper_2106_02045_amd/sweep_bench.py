@@ -45,7 +45,7 @@ def main(argv=None):
     ap.add_argument("--sizes", default="4-32")
     ap.add_argument("--batches", default="10,100,1000,10000")
     ap.add_argument("--plan", default="throughput", choices=["throughput", "latency"],
-                    help="lane mapping: few lanes per spot, or one lane per column")
+                    help="plan hint of the fit (latency: never another mapping than the default one)")
     a = ap.parse_args(argv)
 
     import torch
