@@ -537,6 +537,13 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
     const double x = L.x[slot], y = L.y[slot], hx = L.hx[slot], hy = L.hy[slot];
     const int cslot = slot;
     if constexpr (ANY) win = win_next;
+    if constexpr (RECT) {
+      // formed anew in each pass: the masks of all its rows and columns, held over the
+      // passes, take the scalar registers of the whole kernel
+      asm volatile("" : "+v"(win.h));
+#pragma unroll
+      for (int q = 0; q < CH; ++q) asm volatile("" : "+v"(win.own[q]), "+v"(win.over[q]));
+    }
     if constexpr (kRing) {
       aim(slot);
       if (p < cnt_new) {
@@ -585,7 +592,9 @@ __device__ __forceinline__ void evaluate_uniform(const void* data, Shared<NS>& L
       if constexpr (t < TR) E[t] = vector_entry(ln, lg::gbcast<4, t % 4>(eyq[t / 4]), dy0 + double(4 * t));
       if constexpr (t < TB) GX = mfma4(V[t], V[t], GX);
       if constexpr (t < TR) GY = mfma4(E[t], E[t], GY);
-      if constexpr (t % 4 == 3) __builtin_amdgcn_sched_barrier(0);
+      // (of three: without the first one the loads of the next pass came after the
+      // products, 2 % at 9..12 px)
+      if constexpr (t % 4 == 3 || (TB == 3 && t == 0)) __builtin_amdgcn_sched_barrier(0);
     });
     __builtin_amdgcn_sched_barrier(0);
     if constexpr (!kRing) {
@@ -1280,13 +1289,13 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         if (act) L.order[rank] = own;
         wave_lds_sync();
         const int cnt_new = __builtin_popcountll(m_new);
-        if (small) {
+        if (__builtin_expect(small, 0)) {
           if constexpr (kMany) evaluate_uniform<NS, DT, 2, 2, false, true>(data, L, cnt, cnt_new, geo0);
         } else if (uni) {
           unrolled<4 * CH - 1>([&](auto ti) {
             constexpr int TB = decltype(ti)::value + 2;
             if (T != TB && !(TB == 2 && T < 2)) return;
-            if (!kMany || Tr == TB || (TB == 2 && Tr < 2))
+            if (!kMany || __builtin_expect(Tr == TB || (TB == 2 && Tr < 2), 1))
               evaluate_uniform<NS, DT, TB, TB, false>(data, L, cnt, cnt_new, geo0);
             else if constexpr (kMany)
               evaluate_uniform<NS, DT, TB, 4 * CH, true>(data, L, cnt, cnt_new, geo0);
