@@ -435,8 +435,8 @@ __device__ __forceinline__ Amplitudes slot_amplitudes(const Shared<NS>& L, int s
 // has the shape of geo0, with TB columns per lane group and TR row tiles or, if
 // RECT, at most TR row tiles: those below the spots are branched over (uneven
 // spots of one shape in the passes for mixed shapes, over the tiles of their
-// larger side both ways, / so: 1M of 16-bit 8x32 2.71 ms / 1.21, 16x6 1.21 / 0.82;
-// of float 32x8 4.41 / 2.02, 16x6 1.67 / 1.26; lane-owned 3.61, 1.00, 3.50, 1.01).  Float
+// larger side both ways, / so: 1M of 16-bit 8x32 2.72 ms / 1.30, 16x6 1.21 / 0.84;
+// of float 32x8 4.42 / 2.07, 16x6 1.67 / 1.24; lane-owned 3.61, 1.00, 3.50, 1.01).  Float
 // data: with chi^2 summed over the pixels.  ANY (two tiles each way): slots of any
 // shapes up to 8 x 8.
 //
@@ -1270,8 +1270,8 @@ __device__ __forceinline__ void fit_matrix(const MatrixQueue& mq, Shared<NS>& L)
         constexpr bool kMany = NS > 16;
         const bool uni = (kMany || T == Tr) && __builtin_amdgcn_ballot_w64(act && (geo & 0xffffu) != geo0) == 0;
         // small spots of any shapes go through passes of two tiles, the next one's
-        // pixels ahead: 1M of 4..8 px 810 us of 16-bit pixels (910 in passes by size),
-        // 1015 of floats (1150)
+        // pixels ahead: 1M of 4..8 px 805 us of 16-bit pixels (910 in passes by size),
+        // 994 of floats (1150)
         const bool small = kMany && !uni && __builtin_amdgcn_ballot_w64(act && tiles_of(geo) > 2) == 0;
         int rank = 0;
         if (uni || small) {  // new spots first, so that few passes form their sums of g and g^2
