@@ -368,8 +368,9 @@ bool spotfit_serve::launch_ready() {
     }
   }
   // the results by the copy engine: a kernel's stores to new places of the host's
-  // ring take long (10,000 frames at 1000 fps: p50 / p99 80 / 230 us with a kernel,
-  // 51 / 103 with the engine, 53 / 116 with the engine both ways)
+  // ring take long (10,000 frames at 1000 fps: p50 80 us with a kernel, 51 with the
+  // engine, 53 with the engine both ways; the p99 of the last two, 103 and 116 in one
+  // run each, is within what runs of one build differ by: 122 to 135)
   if (e == hipSuccess && rc == SPOTFIT_OK)
     e = hipMemcpyAsync(hv.params, dv.params, (size_t)kResBytes * nsp, hipMemcpyDeviceToHost, st);
   Batch b;
