@@ -481,9 +481,9 @@ int64_t matrix_resident(const spotfit_ctx_t* ctx, int slots_index, int32_t dtype
 // Large batches of floats in order are what the lane-owned mapping still fits sooner
 // at some sizes, for the second pass of a step here over the pixels, for the
 // residuals.  Lane-owned / here: of 29..32 px from 100,000 spots on (32x32 538 us /
-// 565, 1M 4.05 ms / 4.92, but 400,000 of 17x17 1.55 / 1.05), of up to 16 px from about
-// 500,000 (1M of 7x7 0.68 / 0.79, 4..8 px 0.79 / 0.99, 9x9 1.00 / 1.02, 15x15 1.12 /
-// 1.20, 16x6 1.01 / 1.24; 400,000 of 15x15 0.52 / 0.52).  Nothing on the host tells
+// 565, 1M 3.97 ms / 4.95, but 400,000 of 17x17 1.55 / 1.02), of up to 16 px from about
+// 500,000 (1M of 7x7 0.68 / 0.78, 4..8 px 0.79 / 1.00, 9x9 1.00 / 1.02, 15x15 1.13 /
+// 1.20, 16x6 1.01 / 1.25; 400,000 of 15x15 0.52 / 0.52).  Nothing on the host tells
 // these from the others (32 is max_side's default), and a spot's bits are not to
 // depend on its batch; spotfit_autotune finds them.
 int matrix_slot_index(const spotfit_ctx_t* ctx, int64_t n, int32_t dtype, const spotfit_options_t& o) {
