@@ -59,6 +59,10 @@
 
 #include <type_traits>
 
+// Nothing is fused that the source does not fuse: the compiler does so only within
+// a basic block, which is not the same in every build of the kernel.
+#pragma clang fp contract(off)
+
 #include "spotfit.h"
 #include "spotfit_internal.h"
 #include "lanegroup.h"
